@@ -1097,10 +1097,6 @@ __device__ __forceinline__ void mfma_rows16x32(const double* A, const double* B,
 // ---------------------------------------------------------------------------
 // Triangular solves by one wave with inverted 32 x 32 diagonal blocks.
 //
-// invert_lower32: the inverse of a 32 x 32 lower-triangular block (column-major,
-// leading dimension ld) into out (32 x 32, column-major); lane c < 32 computes
-// column c by forward substitution on the unit vector e_c (fixed order).
-//
 // trsm_rows16_inv solves X L^T = A for 16 rows r0 .. r0+15 over the columns
 // [c0, c1), left-looking over 32-column chunks J:
 //   T   = A[rows, J] - X[rows, c0:J] L[J, c0:J]^T     (FP64 MFMA)
@@ -1112,29 +1108,6 @@ __device__ __forceinline__ void mfma_rows16x32(const double* A, const double* B,
 // doubles of LDS per wave), and X is re-read by the same wave after a
 // workgroup-scope fence.
 // ---------------------------------------------------------------------------
-// rdiag (optional) holds 1 / L[r][r]; the substitution then multiplies instead
-// of dividing.
-__device__ __forceinline__ void invert_lower32(const double* L, int64_t ld, double* out, double (*W)[PW + 1],
-                                               int lane, const double* rdiag = nullptr) {
-  for (int e = lane; e < PW * PW; e += 64) {
-    const int r = e % PW, c = e / PW;
-    W[r][c] = r >= c ? L[(int64_t)c * ld + r] : 0.0;
-  }
-  __builtin_amdgcn_wave_barrier();
-  if (lane < PW) {
-    double y[PW];
-#pragma unroll
-    for (int r = 0; r < PW; ++r) {
-      double v = (r == lane) ? 1.0 : 0.0;
-#pragma unroll
-      for (int m = 0; m < r; ++m) v = fma(-W[r][m], y[m], v);
-      y[r] = rdiag ? v * rdiag[r] : v / W[r][r];
-    }
-#pragma unroll
-    for (int r = 0; r < PW; ++r) out[lane * PW + r] = y[r];
-  }
-}
-
 template <class LoadA, class StoreX>
 __device__ __forceinline__ void trsm_rows16_inv(const double* X, const double* L, int64_t ld, const double* dinv,
                                                 int c0, int c1, int r0, double (*Ts)[PW + 1], int lane, LoadA load_a,
@@ -1197,65 +1170,15 @@ __device__ __forceinline__ void trsm_rows16_inv(const double* X, const double* L
 // ---------------------------------------------------------------------------
 // Blocked POTRF of the FP64 diagonal tile k, spread over several workgroups:
 // the tile is split into SB x SB blocks and, for each block column j,
-//   (a) k_potrf_block  one workgroup factors the diagonal block D_jj, held
-//                      in registers (right-looking over 16-column panels,
-//                      FP64 MFMA for the panel and trailing blocks, the
-//                      16 x 16 diagonal blocks by one wave with lane
-//                      broadcasts); it also inverts the four 32 x 32
-//                      diagonal blocks of D_jj into dinv for the solves below,
+//   (a) k_potrf_block  one workgroup factors the diagonal block D_jj and
+//                      inverts its four 32 x 32 diagonal blocks into dinv for
+//                      the solves below,
 //   (b) k_potrf_panel  the rows below solve X D_jj^T = A, one wave per 16
 //                      rows (trsm_rows16_inv),
 //   (c) k_potrf_syrk   the lower trailing part loses L_{:,j} L_{:,j}^T
 //                      (64 x 64 output blocks, FP64 MFMA).
 // ---------------------------------------------------------------------------
 constexpr int SB = 128;
-
-// 64-bit lane broadcast: the value v of lane src, read as a wave-uniform scalar.
-__device__ __forceinline__ double readlane_f64(double v, int src) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, src);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), src);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// 1 / sqrt(d) for d > 0 (normal): the hardware estimate refined by two
-// Newton steps y <- y + (y / 2)(1 - d y^2), each of which squares the relative
-// error (about 3/2 e^2), so an estimate good to 2^-14 or better ends within a
-// few units in the last place.
-__device__ __forceinline__ double rsqrt_f64(double d) {
-  double y = __builtin_amdgcn_rsq(d);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(-d * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-  }
-  return y;
-}
-
-// Unblocked Cholesky of an N x N block held one row per lane (lane r < N:
-// x[c] = D[r][c], c <= r), by one wave with lane broadcasts and no barriers.
-// The pivot's reciprocal square root r_c gives both L[c][c] = d_c r_c and the
-// column below as multiplications (no divide on the column-to-column chain);
-// rdiag[c] receives r_c = 1 / L[c][c].  Returns the first column whose pivot
-// is not positive, or -1.
-template <int N>
-__device__ __forceinline__ int chol_wave(double (&x)[N], int lane, double* rdiag) {
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    const double d = readlane_f64(x[c], c);
-    if (!(d > 0.0)) return c;
-    const double rs = rsqrt_f64(d);
-    if (lane == 0) rdiag[c] = rs;
-    const double lc = (lane == c) ? d * rs : x[c] * rs;
-    x[c] = lc;
-#pragma unroll
-    for (int q = c + 1; q < N; ++q) {
-      const double lq = readlane_f64(lc, q);
-      if (lane >= q) x[q] = fma(-lc, lq, x[q]);
-    }
-  }
-  return -1;
-}
 
 // acc[h] += A[R0 .. R0+15, K0:K1] * B[C0 + 16h .. C0 + 16h + 15, K0:K1]^T, h < 4,
 // straight from column-major FP64 storage (leading dimension ld), 16 k per
@@ -1291,206 +1214,6 @@ __device__ __forceinline__ void mfma_rows16x64(const double* A, const double* B,
       }
     }
   }
-}
-
-constexpr int PB = 16;  // panel width inside the diagonal block
-
-// The 36 lower 16 x 16 blocks (bi >= bj) of a 128 x 128 diagonal block, by
-// columns; block b belongs to wave b % 4 (its slot b / 4 of nine).
-constexpr int NBLK = (SB / PB) * (SB / PB + 1) / 2;
-__device__ __forceinline__ void blk_ij(int b, int& bi, int& bj) {
-  bj = 0;
-  int rem = b, len = SB / PB;
-  while (rem >= len) { rem -= len; ++bj; --len; }
-  bi = bj + rem;
-}
-
-// Register-resident right-looking factorisation of the diagonal block: every
-// wave holds its nine 16 x 16 blocks in the MFMA result layout for the whole
-// kernel (loaded once, stored once).  Per 16-column panel p:
-//   (1) the owner of block (p, p) factors it by one wave with lane broadcasts
-//       and inverts the 16 x 16 factor (forward substitution on unit vectors);
-//   (2) the owners of the blocks (i, p) below form L_ip = A_ip L_pp^{-T} (FP64
-//       MFMA, the block brought into the operand layout through LDS) and put
-//       L_ip in LDS;
-//   (3) every trailing block (i, j), p < j <= i, loses L_ip L_jp^T (FP64 MFMA
-//       from LDS).
-// Two barriers per panel; the panel's blocks pass through 16 x 17 LDS slots.
-__global__ __launch_bounds__(256) void k_potrf_block(TileView tv, int k, int j, double* dinv) {
-  if (*tv.info) return;
-  const int nb = tv.nb, c0 = j * SB, c1 = c0 + SB;
-  double* A = (double*)tv.tile(k, k);
-  __shared__ double Dg[PB][PB + 1];  // the diagonal block, then its factor
-  __shared__ double Di[PB][PB + 1];  // the factor's inverse
-  __shared__ double Dr[SB];          // 1 / L[c][c] of the block's columns
-  // panel blocks P[i] (16 x 17 each), later the waves' store slots and 32 x 32
-  // inversion space
-  constexpr int PSZ = (SB / PB) * PB * (PB + 1);
-  constexpr int WSZ = 4 * PW * (PW + 1);
-  __shared__ double pool[PSZ > WSZ ? PSZ : WSZ];
-  double (*P)[PB][PB + 1] = (double (*)[PB][PB + 1])pool;
-  __shared__ int fail;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lr = lane >> 4, lc = lane & 15;  // result layout: rows lr + 4 r, column lc
-  if (tid == 0) fail = 0;
-
-  d4 acc[9];
-#pragma unroll
-  for (int sl = 0; sl < 9; ++sl) {
-    const int b = 4 * sl + wave;
-    acc[sl] = d4{0, 0, 0, 0};
-    if (b < NBLK) {
-      int bi, bj;
-      blk_ij(b, bi, bj);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        acc[sl][r] = A[(int64_t)(c0 + PB * bj + lc) * nb + c0 + PB * bi + lr + 4 * r];
-    }
-  }
-  __syncthreads();
-
-#pragma unroll 1
-  for (int p = 0; p < SB / PB; ++p) {
-    // (1) diagonal block (p, p), block index 8p - p(p-1)/2; the factorisation
-    // code is outside the slot loop so that it exists once in the kernel
-    const int bpp = (SB / PB) * p - p * (p - 1) / 2;
-#pragma unroll
-    for (int sl = 0; sl < 9; ++sl)
-      if (4 * sl + wave == bpp) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Dg[lr + 4 * r][lc] = acc[sl][r];
-      }
-    if (wave == bpp % 4) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      double x[PB];
-#pragma unroll
-      for (int c = 0; c < PB; ++c) x[c] = (lane < PB && c <= lane) ? Dg[lane][c] : 0.0;
-      const int bad = chol_wave<PB>(x, lane, Dr + PB * p);
-      if (bad >= 0) {
-        if (lane == 0) {
-          fail = 1;
-          if (*tv.info == 0) *tv.info = k * nb + c0 + PB * p + bad + 1;
-        }
-      } else {
-        if (lane < PB) {
-#pragma unroll
-          for (int c = 0; c < PB; ++c) Dg[lane][c] = c <= lane ? x[c] : 0.0;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (lane < PB) {  // column lane of the inverse
-          double y[PB];
-#pragma unroll
-          for (int r = 0; r < PB; ++r) {
-            double v = (r == lane) ? 1.0 : 0.0;
-#pragma unroll
-            for (int m = 0; m < r; ++m) v = fma(-Dg[r][m], y[m], v);
-            y[r] = v * Dr[PB * p + r];
-          }
-#pragma unroll
-          for (int r = 0; r < PB; ++r) Di[r][lane] = y[r];
-        }
-#pragma unroll
-        for (int sl = 0; sl < 9; ++sl)
-          if (4 * sl + wave == bpp) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[sl][r] = Dg[lr + 4 * r][lc];
-          }
-      }
-    }
-    __syncthreads();
-    if (fail) return;
-    // (2) panel blocks (i, p), i > p
-#pragma unroll
-    for (int sl = 0; sl < 9; ++sl) {
-      const int b = 4 * sl + wave;
-      if (b >= NBLK) continue;
-      int bi, bj;
-      blk_ij(b, bi, bj);
-      if (bj != p || bi == p) continue;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) P[bi][lr + 4 * r][lc] = acc[sl][r];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      d4 xv = {0, 0, 0, 0};
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        xv = __builtin_amdgcn_mfma_f64_16x16x4f64(P[bi][lc][4 * u + lr], Di[lc][4 * u + lr], xv, 0, 0, 0);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      acc[sl] = xv;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) P[bi][lr + 4 * r][lc] = xv[r];
-    }
-    __syncthreads();
-    // (3) trailing blocks (i, j), p < j <= i
-#pragma unroll
-    for (int sl = 0; sl < 9; ++sl) {
-      const int b = 4 * sl + wave;
-      if (b >= NBLK) continue;
-      int bi, bj;
-      blk_ij(b, bi, bj);
-      if (bj <= p) continue;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        acc[sl] = __builtin_amdgcn_mfma_f64_16x16x4f64(-P[bi][lc][4 * u + lr], P[bj][lc][4 * u + lr], acc[sl], 0,
-                                                       0, 0);
-    }
-  }
-
-  // the factor's lower blocks, each turned through a 16 x 17 LDS slot of its
-  // wave so that a lane stores four consecutive rows of one column (a store
-  // instruction then covers whole 128-byte pieces of 16 columns), then zeros
-  // above the diagonal in columns c0 .. c1
-  __syncthreads();  // the panel slots are free once every wave has left (3)
-  {
-    double (*T)[PB + 1] = (double (*)[PB + 1])(pool + wave * PB * (PB + 1));
-    const int tc = lane >> 2, tr = 4 * (lane & 3);
-#pragma unroll
-    for (int sl = 0; sl < 9; ++sl) {
-      const int b = 4 * sl + wave;
-      if (b >= NBLK) continue;
-      int bi, bj;
-      blk_ij(b, bi, bj);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) T[lr + 4 * r][lc] = acc[sl][r];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      double v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = T[tr + e][tc];
-      double* o = A + (int64_t)(c0 + PB * bj + tc) * nb + c0 + PB * bi + tr;
-      if (bi > bj) {
-        *(double2*)o = double2{v[0], v[1]};
-        *(double2*)(o + 2) = double2{v[2], v[3]};
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (tr + e >= tc) o[e] = v[e];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-  }
-  // (one wave per column, two rows per lane and store)
-  for (int c = c0 + wave; c < c1; c += 4)
-    for (int r = 2 * lane; r < c; r += 128) {
-      double* o = A + (int64_t)c * nb + r;
-      if (r + 1 < c) *(double2*)o = double2{0.0, 0.0};
-      else *o = 0.0;
-    }
-  __syncthreads();
-  // inverses of the four 32 x 32 diagonal blocks, one per wave
-  double (*W)[PW][PW + 1] = (double (*)[PW][PW + 1])pool;
-  const int d0 = c0 + wave * PW;
-  invert_lower32(A + (int64_t)d0 * nb + d0, nb, dinv + (int64_t)d0 * PW, W[wave], lane, Dr + wave * PW);
 }
 
 // rows c1 .. nb of block column j: X D_jj^T = A in place, one wave per 16 rows
@@ -1591,7 +1314,7 @@ hipError_t launch_syrk_tile(const TileView& tv, int k, int j, hipStream_t s) {
 hipError_t launch_potrf_tile(const TileView& tv, int k, double* dinv, hipStream_t s) {
   const int nsb = tv.nb / SB;
   for (int j = 0; j < nsb; ++j) {
-    k_potrf_block<<<1, 256, 0, s>>>(tv, k, j, dinv);
+    if (const hipError_t e = launch_potrf_block(tv, k, j, dinv, s); e != hipSuccess) return e;
     const int rest = (tv.nb - (j + 1) * SB) / 64;  // 64-row blocks below block j
     if (rest > 0) {
       k_potrf_panel<<<rest * 4, 64, 0, s>>>(tv, k, j, dinv);

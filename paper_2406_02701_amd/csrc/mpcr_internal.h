@@ -235,6 +235,8 @@ hipError_t launch_convert(int prec, int64_t m, int64_t n, const double* src, int
                           int64_t ldd, int8_t* scale_exp, hipStream_t s);
 
 hipError_t launch_potrf_tile(const TileView& tv, int k, double* dinv, hipStream_t s);
+// the 128 x 128 diagonal block j of that tile (and its four inverted 32 x 32 blocks into dinv)
+hipError_t launch_potrf_block(const TileView& tv, int k, int j, double* dinv, hipStream_t s);
 // A_jj -= L_jk L_jk^T for an FP64 panel tile (j, k)
 hipError_t launch_syrk_tile(const TileView& tv, int k, int j, hipStream_t s);
 // FP8 tiles: per-tile scales from the tile maxima (amax: nt x nt, row-major)
