@@ -4,6 +4,8 @@
 // with one workgroup.  It sits alone on the critical path of every
 // factorisation, so it is built for latency, not for flops (the block's
 // 0.7 MFLOP are 2.3 us of one CU's FP64 MFMA rate).
+#include <type_traits>
+
 #include "mpcr_internal.h"
 
 namespace mpcr {
@@ -18,14 +20,6 @@ constexpr int BLD = PB + 1;  // LDS row of a 16 x 16 block (doubles)
 
 __device__ __forceinline__ int tri_blk(int i, int j) { return i * (i + 1) / 2 + j; }
 
-// 64-bit lane broadcast: the value v of lane src, read as a wave-uniform scalar.
-__device__ __forceinline__ double lane_f64(double v, int src) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, src);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), src);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 // 1 / sqrt(d) for d > 0 (normal): the hardware estimate y, then one step of
 // third order, y (1 + e/2 + 3/8 e^2) with e = 1 - d y^2 (the series of
 // (1 - e)^(-1/2)), whose relative error is about 5/16 e^3: an estimate good to
@@ -37,56 +31,133 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// Sixteen columns of a right-looking Cholesky with one matrix row per lane:
-// lanes 0..15 hold the rows of the 16 x 16 diagonal block, lanes 16..63 rows
-// below it (x[c] = element c of the row), so the rows below are solved by the
-// same operations that factor the block.  The elements above the diagonal are
-// carried along and never used.  rs receives 1 / L[l][l] in lane l < 16.
-// Returns the first column whose pivot is not positive, or -1.
-__device__ __forceinline__ int factor_rows16(double (&x)[PB], int lane, double& rs) {
-#pragma unroll
-  for (int c = 0; c < PB; ++c) {
-    const double d = lane_f64(x[c], c);
-    if (!(d > 0.0)) return c;
-    const double r = rsqrt_f64(d);
-    rs = lane == c ? r : rs;
-    const double lc = x[c] * r;
-    x[c] = lc;
-#pragma unroll
-    for (int q = c + 1; q < PB; ++q) x[q] = fma(-lc, lane_f64(lc, q), x[q]);
+// Column steps with lane N of every 16-lane row broadcast to that row inside
+// the operation (DPP row_newbcast; no trip through scalar registers).  A DPP
+// operand must have been written two wait states before its use: every block
+// sees to that itself.
+//   fma2_bcast<Q>   d[q] -= d_C[q] d_C,  x[q] -= d_C[q] x_C  for q = Q .. 15
+//                   (s = d_C, t = x_C; d_C[q] is lane q's value)
+template <int Q>
+__device__ __forceinline__ void fma2_bcast(double (&d)[PB], double (&x)[PB], double s, double t) {
+  if constexpr (Q + 5 <= PB) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, -%10, %10 row_newbcast:%c12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %5, -%10, %11 row_newbcast:%c12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, -%10, %10 row_newbcast:%c13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %6, -%10, %11 row_newbcast:%c13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, -%10, %10 row_newbcast:%c14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %7, -%10, %11 row_newbcast:%c14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, -%10, %10 row_newbcast:%c15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %8, -%10, %11 row_newbcast:%c15 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %4, -%10, %10 row_newbcast:%c16 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %9, -%10, %11 row_newbcast:%c16 row_mask:0xf bank_mask:0xf"
+        : "+v"(d[Q]), "+v"(d[Q + 1]), "+v"(d[Q + 2]), "+v"(d[Q + 3]), "+v"(d[Q + 4]), "+v"(x[Q]), "+v"(x[Q + 1]), "+v"(x[Q + 2]), "+v"(x[Q + 3]), "+v"(x[Q + 4])
+        : "v"(s), "v"(t), "n"(Q), "n"(Q + 1), "n"(Q + 2), "n"(Q + 3), "n"(Q + 4));
+    fma2_bcast<Q + 5>(d, x, s, t);
+  } else if constexpr (Q + 2 <= PB) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, -%4, %4 row_newbcast:%c6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, -%4, %5 row_newbcast:%c6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, -%4, %4 row_newbcast:%c7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, -%4, %5 row_newbcast:%c7 row_mask:0xf bank_mask:0xf"
+        : "+v"(d[Q]), "+v"(d[Q + 1]), "+v"(x[Q]), "+v"(x[Q + 1])
+        : "v"(s), "v"(t), "n"(Q), "n"(Q + 1));
+    fma2_bcast<Q + 2>(d, x, s, t);
+  } else if constexpr (Q + 1 <= PB) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, -%2, %2 row_newbcast:%c4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, -%2, %3 row_newbcast:%c4 row_mask:0xf bank_mask:0xf"
+        : "+v"(d[Q]), "+v"(x[Q])
+        : "v"(s), "v"(t), "n"(Q));
+    fma2_bcast<Q + 1>(d, x, s, t);
   }
-  return -1;
+}
+//   column<C>       d_C *= r, x_C *= r, their products with lane C + 1 from d[C + 1]
+//                   and x[C + 1], and returns lane C + 1 of the new d[C + 1]: the next pivot
+template <int C>
+__device__ __forceinline__ double column(double (&d)[PB], double (&x)[PB], double r) {
+  double piv;
+  asm volatile(
+        "v_mul_f64 %0, %0, %5\n\t"
+        "v_mul_f64 %1, %1, %5\n\t"
+        "s_nop 0\n\t"
+        "v_fmac_f64_dpp %2, -%0, %0 row_newbcast:%c6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, -%0, %1 row_newbcast:%c6 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 0\n\t"
+        "v_mov_b64_dpp %4, %2 row_newbcast:%c6 row_mask:0xf bank_mask:0xf"
+        : "+v"(d[C]), "+v"(x[C]), "+v"(d[C + 1]), "+v"(x[C + 1]), "=&v"(piv)
+        : "v"(r), "n"(C + 1));
+  return piv;
 }
 
+// Column C and the following ones of a right-looking Cholesky of a 16 x 16
+// block with the solve of 64 rows below it: d[c] is element c of row lane % 16
+// of the block (every 16-lane row of the wave holds a copy), x[c] element c of
+// this lane's row below.  The rows below are solved by the same column steps
+// that factor the block.  Elements above the diagonal are carried along and
+// never used.  r is 1 / sqrt of column C's pivot; the next pivot and its
+// reciprocal square root come first in a column, so that their latency lies
+// behind the column's other updates, and no branch separates the columns.  A
+// pivot that is not positive (or infinite) makes r and everything after it
+// NaN, which the last r, returned, shows.  TRACK: bad collects the columns
+// whose pivot is not positive as bits.
+template <int C, bool TRACK>
+__device__ __forceinline__ double factor_rows16(double (&d)[PB], double (&x)[PB], double r, uint32_t& bad) {
+  if constexpr (C + 1 < PB) {
+    const double piv = column<C>(d, x, r);
+    const double rn = rsqrt_f64(piv);
+    if (TRACK) bad |= (uint32_t)(__builtin_amdgcn_ballot_w64(!(piv > 0.0)) & 1u) << (C + 1);
+    fma2_bcast<C + 2>(d, x, d[C], x[C]);
+    return factor_rows16<C + 1, TRACK>(d, x, rn, bad);
+  } else {
+    d[C] *= r;
+    x[C] *= r;
+    return r;
+  }
+}
+
+struct PotrfLds {
+  double L[NP * (NP + 1) / 2][PB][BLD];  // the lower 16 x 16 blocks
+  double Di[4][PB][BLD];                 // inverses of the factored diagonal blocks p (slot p % 4)
+  int fail;
+};
+
 // The block's 36 lower 16 x 16 blocks live in LDS.  Per 16-column panel p:
-//   (1) up to three waves factor it: every one of them holds the 16 rows of
-//       the diagonal block (p, p) in lanes 0..15 and 48 rows below it in lanes
-//       16..63 (the factorisation of the diagonal block is repeated in each,
-//       which costs nothing and needs no exchange between waves); meanwhile
-//       the other waves finish the trailing update with panel p - 1 and the
-//       inverses of the diagonal blocks;
-//   (2) all waves subtract panel p's product from the blocks of column p + 1
-//       (FP64 MFMA), the next panel to be factored.
+//   (1) one or two waves factor it: each holds the diagonal block (p, p) and 64
+//       rows to be solved with it (the factorisation of the diagonal block is
+//       repeated in both, which needs no exchange between them).  The rows are
+//       those of the panel below and, behind them, the 16 rows of a unit
+//       matrix, whose solution is the inverse of the diagonal block.
+//       Meanwhile the other waves finish the trailing update with panel p - 1
+//       and store that panel;
+//   (2) the blocks of column p + 1, the next panel, lose panel p's product
+//       (FP64 MFMA, one wave each).
 // Two barriers per panel; the chain per panel is the sixteen columns of (1)
-// and one block product of (2).  dinv receives the inverses of the four
-// 32 x 32 diagonal blocks, [[A', 0], [-C' B A', C']] from the 16 x 16 ones.
-// 86 KB of LDS and at most 128 VGPRs: with the tile updates resident on every
-// CU (two workgroups of 74 KB), it fits as soon as one of them retires.
-__global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(128))) void k_potrf_block(TileView tv, int k, int j,
-                                                                                           double* dinv) {
-  if (*tv.info) return;
+// (about 150 cycles each, nearly all of it instruction issue) and one block
+// product of (2).  Measured alone: 23 us a block (87 us for a version that
+// inverted each diagonal block and solved the panel by MFMA afterwards).  dinv receives the inverses of the four 32 x 32 diagonal blocks,
+// [[A', 0], [-C' B A', C']] from the 16 x 16 ones.  Nothing above the diagonal
+// is written (no kernel reads it).
+// 87 KB of LDS and at most 128 VGPRs: with the tile updates resident on every
+// CU (two workgroups of 74 KB), it fits as soon as one of them retires.  (The
+// LDS is given at the launch: counted by the compiler, it would make it spend
+// 256 VGPRs.)
+__global__ __launch_bounds__(512, 4) void k_potrf_block(TileView tv, int k, int j, double* dinv) {
+  const int info0 = *tv.info;
   const int nb = tv.nb, c0 = j * SB;
   double* A = (double*)tv.tile(k, k) + (int64_t)c0 * nb + c0;
-  __shared__ __attribute__((aligned(16))) double L[NP * (NP + 1) / 2][PB][BLD];
-  __shared__ double Dg[PB][BLD];     // the diagonal block that the panel's first wave has factored
-  __shared__ double Di[2][PB][BLD];  // inverses of the diagonal blocks p (slot p % 2)
-  __shared__ double Dr[SB];          // 1 / L[c][c]
-  __shared__ int fail;
+  extern __shared__ __attribute__((aligned(16))) char potrf_lds[];
+  PotrfLds& sm = *(PotrfLds*)potrf_lds;
+  auto& L = sm.L;
+  auto& Di = sm.Di;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15;  // MFMA result: rows lr + 4 r, column lc
-  if (tid == 0) fail = 0;
 
-  // load: one wave per column, two rows per lane (column pieces of 1 KB)
+  // load: one wave per column, two rows per lane (column pieces of 1 KB); the
+  // info word is looked at only once these loads are on their way
   {
     double2 v[SB / 8];
     const int bi = lane >> 3, r = 2 * (lane & 7);
@@ -95,6 +166,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(128))) void k_p
       const int c = wave + 8 * g;
       if (bi >= c / PB) v[g] = *(const double2*)(A + (int64_t)c * nb + 2 * lane);
     }
+    if (info0) return;
+    if (tid == 0) sm.fail = 0;
 #pragma unroll
     for (int g = 0; g < SB / 8; ++g) {
       const int c = wave + 8 * g, bj = c / PB;
@@ -106,144 +179,138 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(128))) void k_p
   }
   __syncthreads();
 
-  // block (bi, bj) -= L(bi, p) L(bj, p)^T
-  auto update = [&](int bi, int bj, int p) {
-    double(*C)[BLD] = L[tri_blk(bi, bj)];
-    const double(*P)[BLD] = L[tri_blk(bi, p)];
-    const double(*Q)[BLD] = L[tri_blk(bj, p)];
-    double a[4], b[4];
-    d4 acc;
+  // blocks (bi, bj) -= L(bi, p) L(bj, p)^T for the N given blocks
+  auto update = [&](auto ntag, const int (&bi)[2], const int (&bj)[2], int p) {
+    constexpr int N = decltype(ntag)::value;
+    d4 acc[N];
+    double a[N][4], b[N][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r] = C[lr + 4 * r][lc];
+    for (int n = 0; n < N; ++n)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a[u] = -P[lc][4 * u + lr];
-      b[u] = Q[lc][4 * u + lr];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) C[lr + 4 * r][lc] = acc[r];
-  };
-  // Di[p % 2] = L(p, p)^{-1}, column `lane` by forward substitution (one wave)
-  auto invert16 = [&](int p) {
-    const double(*D)[BLD] = L[tri_blk(p, p)];
-    if (lane < PB) {
-      double y[PB];
-#pragma unroll
-      for (int r = 0; r < PB; ++r) y[r] = r == lane ? 1.0 : 0.0;
-#pragma unroll
-      for (int r = 0; r < PB; ++r) {
-        y[r] *= Dr[PB * p + r];
-#pragma unroll
-        for (int q = r + 1; q < PB; ++q) y[q] = fma(-D[q][r], y[r], y[q]);
+      for (int u = 0; u < 4; ++u) {
+        a[n][u] = -L[tri_blk(bi[n], p)][lc][4 * u + lr];
+        b[n][u] = L[tri_blk(bj[n], p)][lc][4 * u + lr];
+        acc[n][u] = L[tri_blk(bi[n], bj[n])][lr + 4 * u][lc];
       }
 #pragma unroll
-      for (int r = 0; r < PB; ++r) Di[p & 1][r][lane] = y[r];
-    }
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int n = 0; n < N; ++n) acc[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[n][u], b[n][u], acc[n], 0, 0, 0);
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) L[tri_blk(bi[n], bj[n])][lr + 4 * u][lc] = acc[n][u];
   };
-  // the inverted 32 x 32 block of the panels p - 1, p (p odd) into dinv (column-major; one wave)
-  auto invert32 = [&](int p) {
-    const double(*B)[BLD] = L[tri_blk(p, p - 1)];
-    d4 t = {0, 0, 0, 0}, m = {0, 0, 0, 0};
-#pragma unroll
-    for (int u = 0; u < 4; ++u) t = __builtin_amdgcn_mfma_f64_16x16x4f64(B[lc][4 * u + lr], Di[0][4 * u + lr][lc], t, 0, 0, 0);
-    // the result layout of t (rows lr + 4 u) is the operand layout of its u-th k step
-#pragma unroll
-    for (int u = 0; u < 4; ++u) m = __builtin_amdgcn_mfma_f64_16x16x4f64(-Di[1][lc][4 * u + lr], t[u], m, 0, 0, 0);
-    double* o = dinv + (int64_t)(c0 + PB * (p - 1)) * PW + lc * PW;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int R = lr + 4 * r;
-      o[R] = Di[0][R][lc];
-      o[PB + R] = m[r];
-      o[PB * PW + R] = 0.0;
-      o[PB * PW + PB + R] = Di[1][R][lc];
-    }
-  };
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 2> two{};
 
 #pragma unroll 1
-  for (int p = 0; p < NP; ++p) {
-    const int below = SB - PB * (p + 1);                     // rows below the diagonal block
-    const int nw = below > 96 ? 3 : below > 48 ? 2 : 1;      // waves that factor the panel
+  for (int p = 0; p <= NP; ++p) {
+    const int below = SB - PB * (p + 1);                 // rows below the diagonal block
+    const int nw = p == NP ? 0 : below >= 64 ? 2 : 1;    // waves that factor the panel
+    double d[PB], x[PB];
+    const int t = wave * 64 + lane;                      // row below the diagonal block
     if (wave < nw) {
       __builtin_amdgcn_s_setprio(3);
-      const int t = wave * 48 + lane - PB;  // row below the diagonal block (lanes 16 ..)
-      const bool live = lane < PB || t < below;
-      double(*row)[BLD] = lane < PB ? L[tri_blk(p, p)] + lane : L[tri_blk(p + 1 + (live ? t : 0) / PB, p)] + (live ? t : 0) % PB;
-      if (!live) row = L[tri_blk(p, p)];
-      double x[PB], rs = 0.0;
+      const double* drow = L[tri_blk(p, p)][lc];
+      const double* row = L[tri_blk(p + (t < below ? 1 + t / PB : 0), p)][lc];
 #pragma unroll
-      for (int c = 0; c < PB; ++c) x[c] = (*row)[c];
-      const int bad = factor_rows16(x, lane, rs);
-      if (bad >= 0) {
-        if (tid == 0) {
-          fail = 1;
-          if (*tv.info == 0) *tv.info = k * nb + c0 + PB * p + bad + 1;
+      for (int c = 0; c < PB; ++c) d[c] = drow[c];
+#pragma unroll
+      for (int c = 0; c < PB; ++c) x[c] = row[c];
+      if (t >= below) {
+#pragma unroll
+        for (int c = 0; c < PB; ++c) x[c] = t - below == c ? 1.0 : 0.0;
+      }
+      uint32_t bad = 0;
+      const double rl = factor_rows16<0, false>(d, x, rsqrt_f64(L[tri_blk(p, p)][0][0]), bad);
+      if (!(rl > 0.0)) {  // (uniform) find the first column whose pivot is not positive
+#pragma unroll
+        for (int c = 0; c < PB; ++c) d[c] = drow[c];
+        const double piv = L[tri_blk(p, p)][0][0];
+        bad = __builtin_amdgcn_ballot_w64(!(piv > 0.0)) & 1u;
+        factor_rows16<0, true>(d, x, rsqrt_f64(piv), bad);
+        if (bad && tid == 0) {
+          sm.fail = 1;
+          *tv.info = k * nb + c0 + PB * p + __builtin_ctz(bad) + 1;
         }
-      } else {
-        if (lane >= PB && live) {
+      }
+      if (t < below) {
+        double* o = L[tri_blk(p + 1 + t / PB, p)][lc];
 #pragma unroll
-          for (int c = 0; c < PB; ++c) (*row)[c] = x[c];
-        } else if (lane < PB && wave == 0) {  // (the other waves may still be reading block (p, p))
+        for (int c = 0; c < PB; ++c) o[c] = x[c];
+      } else if (t < below + PB) {
 #pragma unroll
-          for (int c = 0; c < PB; ++c) Dg[lane][c] = c <= lane ? x[c] : 0.0;
-          Dr[PB * p + lane] = rs;
-        }
+        for (int c = 0; c < PB; ++c) Di[p & 3][c][t - below] = x[c];
       }
       __builtin_amdgcn_s_setprio(0);
     } else if (p > 0) {
-      // trailing blocks (bi, bj), p < bj <= bi, with panel p - 1; the last wave
-      // first inverts the diagonal block p - 1
-      if (wave == 7) {
-        invert16(p - 1);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if ((p - 1) & 1) invert32(p - 1);
-      }
-      const int m = NP - 1 - p, nblk = m * (m + 1) / 2;
-      for (int b = wave - nw; b < nblk; b += 8 - nw) {
-        int i = 0, rem = b;
-        while (rem > i) { rem -= i + 1; ++i; }
-        update(p + 1 + i, p + 1 + rem, p - 1);
-      }
-    }
-    __syncthreads();
-    if (fail) return;
-    const int bi = p + 1 + wave;
-    if (bi < NP) update(bi, p + 1, p);
-    if (wave == 7) {  // never has a block above: the factored diagonal block takes its place
+      // the inverted 32 x 32 block of the panels p - 2, p - 1 into dinv (column-major)
+      if (wave == 7 && p % 2 == 0) {
+        const double(*B)[BLD] = L[tri_blk(p - 1, p - 2)];
+        const double(*A0)[BLD] = Di[(p - 2) & 3], (*C0)[BLD] = Di[(p - 1) & 3];
+        d4 s = {0, 0, 0, 0}, m = {0, 0, 0, 0};
 #pragma unroll
-      for (int e = lane; e < PB * PB; e += 64) L[tri_blk(p, p)][e / PB][e % PB] = Dg[e / PB][e % PB];
+        for (int u = 0; u < 4; ++u) s = __builtin_amdgcn_mfma_f64_16x16x4f64(B[lc][4 * u + lr], A0[4 * u + lr][lc], s, 0, 0, 0);
+        // the result layout of s (rows lr + 4 u) is the operand layout of its u-th k step
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m = __builtin_amdgcn_mfma_f64_16x16x4f64(-C0[lc][4 * u + lr], s[u], m, 0, 0, 0);
+        double* o = dinv + (int64_t)(c0 + PB * (p - 2)) * PW + lc * PW;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int R = lr + 4 * r;
+          o[R] = R >= lc ? A0[R][lc] : 0.0;
+          o[PB + R] = m[r];
+          o[PB * PW + R] = 0.0;
+          o[PB * PW + PB + R] = R >= lc ? C0[R][lc] : 0.0;
+        }
+      }
+      // trailing blocks (bi, bj), p < bj <= bi, with panel p - 1
+      const int m = NP - 1 - p, nblk = m * (m + 1) / 2, step = 8 - nw;
+#pragma unroll 1
+      for (int b = wave - nw; b < nblk; b += 2 * step) {
+        int bi[2], bj[2];
+        const bool both = b + step < nblk;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          int i = 0, rem = n && both ? b + step : b;
+          while (rem > i) { rem -= i + 1; ++i; }
+          bi[n] = p + 1 + i;
+          bj[n] = p + 1 + rem;
+        }
+        if (both) update(two, bi, bj, p - 1);
+        else update(one, bi, bj, p - 1);
+      }
+      // panel p - 1 to memory: one wave per column, two rows per lane
+      const int R = PB * (p - 1) + 2 * lane, rb = R < SB ? R / PB : 0;
+      for (int c = wave - nw; c < PB; c += step) {
+        const double v0 = L[tri_blk(rb >= p - 1 ? rb : p - 1, p - 1)][R % PB][c];
+        const double v1 = L[tri_blk(rb >= p - 1 ? rb : p - 1, p - 1)][R % PB + 1][c];
+        double* o = A + (int64_t)(PB * (p - 1) + c) * nb + R;
+        if (R < SB && 2 * lane >= c) *(double2*)o = double2{v0, v1};
+        else if (R < SB && 2 * lane + 1 == c) o[1] = v1;
+      }
+    }
+    if (p == NP) break;
+    __syncthreads();
+    if (sm.fail) return;
+    if (wave > 0 && p + wave < NP) {
+      const int bi[2] = {p + wave, 0}, bj[2] = {p + 1, 0};
+      update(one, bi, bj, p);
+    }
+    if (wave == 0) {
+      // the factored diagonal block, only now that no wave reads the old one:
+      // every 16-lane row stores four columns of its copy
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        L[tri_blk(p, p)][lc][4 * lr + c] = lr == 0 ? d[c] : lr == 1 ? d[4 + c] : lr == 2 ? d[8 + c] : d[12 + c];
     }
     __syncthreads();
-  }
-
-  if (wave == 7) {
-    invert16(NP - 1);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    invert32(NP - 1);
-  }
-  // store: one wave per column, two rows per lane; nothing above the diagonal
-  // is written (no kernel reads it)
-  {
-    const int bi = lane >> 3, r = 2 * (lane & 7);
-    for (int c = wave; c < SB; c += 8) {
-      const int bj = c / PB;
-      if (2 * lane + 1 < c) continue;
-      double* o = A + (int64_t)c * nb + 2 * lane;
-      const double v0 = L[tri_blk(bi, bj)][r][c % PB], v1 = L[tri_blk(bi, bj)][r + 1][c % PB];
-      if (2 * lane >= c) *(double2*)o = double2{v0, v1};
-      else o[1] = v1;
-    }
   }
 }
 
 hipError_t launch_potrf_block(const TileView& tv, int k, int j, double* dinv, hipStream_t s) {
-  k_potrf_block<<<1, 512, 0, s>>>(tv, k, j, dinv);
+  k_potrf_block<<<1, 512, sizeof(PotrfLds), s>>>(tv, k, j, dinv);
   return hipGetLastError();
 }
 
