@@ -2103,15 +2103,16 @@ int mpcr_gemm(mpcr_ctx* ctx, mpcr_prec_t prec, int transA, int transB, int64_t m
     return MPCR_OK;
   }
   // 16/8-bit: the kernel reads op(A) as m x k and op(B) as n x k arrays with k
-  // contiguous and 16-byte aligned rows; operands in another layout are packed
-  // into a workspace first (one pass over each, small next to the product).
+  // contiguous, 16-byte aligned rows and whole stages of k; operands in another
+  // layout are packed into a workspace first (one pass over each, small next to
+  // the product), k padded with zeros.
   const int es = (p == F8) ? 1 : 2;
+  const int64_t kst = gemm_lowp_kstage(p), kp = (k + kst - 1) / kst * kst;
   auto usable = [&](const void* ptr, int64_t ld, bool kcontig) {
-    return kcontig && ((uintptr_t)ptr % 16 == 0) && ((ld * es) % 16 == 0);
+    return kcontig && k == kp && ((uintptr_t)ptr % 16 == 0) && ((ld * es) % 16 == 0);
   };
   const bool a_ok = usable(d_A, lda, transA != 0), b_ok = usable(d_B, ldb, transB == 0);
-  const int64_t ldk = (k + 15) / 16 * 16;  // packed leading dimension (elements)
-  const int64_t a_bytes = a_ok ? 0 : (m * ldk * es + 255) / 256 * 256, b_bytes = b_ok ? 0 : n * ldk * es;
+  const int64_t a_bytes = a_ok ? 0 : (m * kp * es + 255) / 256 * 256, b_bytes = b_ok ? 0 : n * kp * es;
   if (ctx->ws_gemm_bytes < a_bytes + b_bytes) {
     HIP_TRY(ctx, hipStreamSynchronize(s));
     dfree(ctx->arena, ctx->ws_gemm);
@@ -2124,20 +2125,20 @@ int mpcr_gemm(mpcr_ctx* ctx, mpcr_prec_t prec, int transA, int transB, int64_t m
   int64_t ldat = lda;
   if (!a_ok) {
     A = ctx->ws_gemm;
-    ldat = ldk;
-    HIP_TRY(ctx, launch_pack(es, transA == 0, m, k, d_A, lda, ctx->ws_gemm, ldk, s));
+    ldat = kp;
+    HIP_TRY(ctx, launch_pack(es, transA == 0, m, k, d_A, lda, ctx->ws_gemm, kp, s));
   }
   const void* B = d_B;
   int64_t ldbk = ldb;
   if (!b_ok) {
     B = ctx->ws_gemm + a_bytes;
-    ldbk = ldk;
-    HIP_TRY(ctx, launch_pack(es, transB != 0, n, k, d_B, ldb, ctx->ws_gemm + a_bytes, ldk, s));
+    ldbk = kp;
+    HIP_TRY(ctx, launch_pack(es, transB != 0, n, k, d_B, ldb, ctx->ws_gemm + a_bytes, kp, s));
   }
   // FP8 scale grids belong to the stored matrices (column-major over 128 x 128 blocks)
   const int64_t mbA = transA ? (k + 127) / 128 : (m + 127) / 128;
   const int64_t mbB = transB ? (n + 127) / 128 : (k + 127) / 128;
-  HIP_TRY(ctx, launch_gemm_lowp(p, m, n, k, alpha, A, ldat, d_scaleA_exp, mbA, transA != 0, B, ldbk, d_scaleB_exp,
+  HIP_TRY(ctx, launch_gemm_lowp(p, m, n, kp, alpha, A, ldat, d_scaleA_exp, mbA, transA != 0, B, ldbk, d_scaleB_exp,
                                 mbB, transB != 0, beta, d_C, ldc, cp, s));
   return MPCR_OK;
 }
