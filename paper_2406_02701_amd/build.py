@@ -30,7 +30,7 @@ CFLAGS = [
 ]
 # roctx ranges (rocprofiler-sdk)
 LINK_FLAGS = ["-L/opt/rocm/lib", "-lrocprofiler-sdk-roctx"]
-SOURCES = ["tiles.hip", "factor.hip", "panel.hip", "solve.hip", "order.hip", "gemm.hip", "laplace.hip", "mala.hip", "krylov.hip", "api.cpp", "serve.cpp"]
+SOURCES = ["tiles.hip", "update.hip", "factor.hip", "panel.hip", "solve.hip", "order.hip", "gemm.hip", "laplace.hip", "mala.hip", "krylov.hip", "api.cpp", "serve.cpp"]
 
 
 def _compile(src: str) -> str:

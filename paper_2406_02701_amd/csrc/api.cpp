@@ -493,7 +493,7 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
         const uint16_t* sp = p == F32 ? f->d_split + (k & 1) * split_stride : f->d_b16 + (k & 1) * b16_stride;
         HIP_TRY(ctx, timed(ctx, s, p, fl, [&] { return launch_tile_update_packed(tv, (int)k, p, t, cnt, sp, s); }));
       } else {
-        HIP_TRY(ctx, timed(ctx, s, p, fl, [&] { return launch_tile_update(tv, (int)k, p, t, cnt, s, ctx->fp32_split); }));
+        HIP_TRY(ctx, timed(ctx, s, p, fl, [&] { return launch_tile_update(tv, (int)k, p, t, cnt, s); }));
       }
     }
     return MPCR_OK;

@@ -29,63 +29,11 @@ typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 //   result f64: lane l, register r -> D[l/16 + 4r][l%16]
 
 // ---------------------------------------------------------------------------
-// operand conversion on load (A7a: the update runs in the output tile's format)
-// ---------------------------------------------------------------------------
-template <int CF> struct CTraits;
-template <> struct CTraits<F64> { using T = double; };
-template <> struct CTraits<F32> { using T = float; };
-template <> struct CTraits<BF16> { using T = uint16_t; };
-template <> struct CTraits<F16> { using T = uint16_t; };
-
-template <int CF>
-__device__ __forceinline__ typename CTraits<CF>::T load_as(const void* p, int f, int64_t idx) {
-  if constexpr (CF == F64) {
-    return load_wide(p, f, idx);
-  } else if constexpr (CF == F32) {
-    if (f == F32) return ((const float*)p)[idx];
-    return to_f32(load_wide(p, f, idx));
-  } else if constexpr (CF == BF16) {
-    if (f == BF16) return ((const uint16_t*)p)[idx];
-    if (f == F32) return f32_to_bf16_rne(((const float*)p)[idx]);
-    return to_bf16(load_wide(p, f, idx));
-  } else {
-    if (f == F16) return ((const uint16_t*)p)[idx];
-    if (f == F32) return __builtin_bit_cast(uint16_t, (_Float16)((const float*)p)[idx]);
-    return to_f16(load_wide(p, f, idx));
-  }
-}
-
-// ---------------------------------------------------------------------------
-// batched tile update  C(i,j) -= A(i,k) B(j,k)^T, one 128 x 128 block of C per
-// workgroup (4 waves, 2 x 2, each 64 x 64 = 4 x 4 MFMA tiles of 16 x 16)
+// batched tile update  C(i,j) -= A(i,k) B(j,k)^T of 16-bit and FP8 tiles (FP64
+// and FP32: update.hip), one 128 x 128 block of C per workgroup (4 waves,
+// 2 x 2, each 64 x 64 = 4 x 4 MFMA tiles of 16 x 16)
 // ---------------------------------------------------------------------------
 constexpr int UBM = 128;
-
-// Four consecutive elements (idx % 4 == 0) of a tile stored in format SF,
-// converted to the compute type of CF with one vector load.
-template <int CF, int SF>
-__device__ __forceinline__ void load4(const void* p, int64_t idx, typename CTraits<CF>::T out[4]) {
-  using T = typename CTraits<CF>::T;
-  if constexpr (SF == F64) {
-    const double4 v = *(const double4*)((const double*)p + idx);
-    const double w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int r = 0; r < 4; ++r) out[r] = (CF == F64) ? (T)w[r] : (T)to_f32(w[r]);
-  } else if constexpr (SF == F32) {
-    const float4 v = *(const float4*)((const float*)p + idx);
-    out[0] = (T)v.x; out[1] = (T)v.y; out[2] = (T)v.z; out[3] = (T)v.w;
-  } else if constexpr (SF == F16 || SF == BF16) {
-    const ushort4 v = *(const ushort4*)((const uint16_t*)p + idx);
-    const uint16_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int r = 0; r < 4; ++r) out[r] = (T)(SF == F16 ? f16_to_f32(w[r]) : bf16_to_f32(w[r]));
-  } else {
-    const uchar4 v = *(const uchar4*)((const uint8_t*)p + idx);
-    const uint8_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int r = 0; r < 4; ++r) out[r] = (T)e4m3_to_f32(w[r]);
-  }
-}
 
 // C[idx] <- round_f(C[idx] - acc) for the epilogue, with a static format.
 template <int F>
@@ -95,172 +43,6 @@ __device__ __forceinline__ void rmw_sub(void* Cp, int64_t idx, double acc) {
   else if constexpr (F == F16) { uint16_t* c = (uint16_t*)Cp; c[idx] = to_f16((double)f16_to_f32(c[idx]) - acc); }
   else if constexpr (F == BF16) { uint16_t* c = (uint16_t*)Cp; c[idx] = to_bf16((double)bf16_to_f32(c[idx]) - acc); }
   else { uint8_t* c = (uint8_t*)Cp; c[idx] = to_e4m3((double)e4m3_to_f32(c[idx]) - acc); }
-}
-
-// FP64 / FP32: operands staged k-major in LDS ([k][m]), double-buffered;
-// fragments are contiguous across lanes.  The main loop is instantiated per
-// pair of operand formats (one branch per workgroup), so each variant holds
-// only its own staging registers.  Shapes (measured on a full-size batch of
-// 2016 tile updates): FP64 uses 8 waves of 64 x 32 (the FP64 MFMA is slow
-// enough that more waves per CU, not more work per wave, hides the staging),
-// FP32 4 waves of 64 x 64 with 16-wide k chunks (four workgroups per CU).
-template <int CF> struct KMajor {
-  using T = typename CTraits<CF>::T;
-  static constexpr int NW = (CF == F64) ? 8 : 4;   // waves per workgroup
-  static constexpr int WM = 2;                      // waves along m
-  static constexpr int WN = NW / WM;
-  static constexpr int TM = UBM / WM, TN = UBM / WN;  // per-wave block
-  static constexpr int FM = TM / 16, FN = TN / 16;    // MFMA tiles per wave
-  static constexpr int NT = NW * 64;
-  static constexpr int BK = 16;
-  // row padding: a fragment read covers 4 consecutive k rows of 16 elements;
-  // the padding puts those rows on disjoint LDS banks
-  static constexpr int PAD = 16;
-  static constexpr int LD = UBM * BK / 4 / NT;  // 4-element loads per thread per operand
-  using Acc = typename std::conditional<CF == F64, d4, f4>::type;
-  using Buf = T[2][BK][UBM + PAD];
-};
-
-template <int CF, int FA, int FB>
-__device__ __forceinline__ void kmajor_mainloop(const void* Ap, const void* Bp, double ma, double mb, int nb,
-                                                int64_t arow0, int64_t brow0,
-                                                typename KMajor<CF>::Buf& As, typename KMajor<CF>::Buf& Bs,
-                                                typename KMajor<CF>::Acc (&acc)[KMajor<CF>::FM][KMajor<CF>::FN]) {
-  using K = KMajor<CF>;
-  using T = typename K::T;
-  constexpr int BK = K::BK, LD = K::LD, NT = K::NT;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % K::WM, wn = wave / K::WM;
-  T ra[LD][4], rb[LD][4];
-  // load e = tid + NT g: rows 4 (e % 32) .. +3 of column e / 32 of the chunk
-  auto gload = [&](int kk) {
-#pragma unroll
-    for (int g = 0; g < LD; ++g) {
-      const int e = tid + NT * g, r = (e % (UBM / 4)) * 4, k = e / (UBM / 4);
-      load4<CF, FA>(Ap, (int64_t)(kk + k) * nb + arow0 + r, ra[g]);
-      load4<CF, FB>(Bp, (int64_t)(kk + k) * nb + brow0 + r, rb[g]);
-      if constexpr (FA == F8) {  // FP8 tiles hold codes of v 2^s: scale back (exact)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) ra[g][u] = (T)((double)ra[g][u] * ma);
-      }
-      if constexpr (FB == F8) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) rb[g][u] = (T)((double)rb[g][u] * mb);
-      }
-    }
-  };
-  auto sstore = [&](int buf) {
-#pragma unroll
-    for (int g = 0; g < LD; ++g) {
-      const int e = tid + NT * g, r = (e % (UBM / 4)) * 4, k = e / (UBM / 4);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        As[buf][k][r + u] = ra[g][u];
-        Bs[buf][k][r + u] = rb[g][u];
-      }
-    }
-  };
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  int cur = 0;
-  for (int kk = 0; kk < nb; kk += BK) {
-    const bool more = kk + BK < nb;
-    if (more) gload(kk + BK);
-#pragma unroll
-    for (int k4 = 0; k4 < BK; k4 += 4) {
-      T av[K::FM], bv[K::FN];
-#pragma unroll
-      for (int a = 0; a < K::FM; ++a) av[a] = As[cur][k4 + (lane >> 4)][wm * K::TM + a * 16 + (lane & 15)];
-#pragma unroll
-      for (int b = 0; b < K::FN; ++b) bv[b] = Bs[cur][k4 + (lane >> 4)][wn * K::TN + b * 16 + (lane & 15)];
-#pragma unroll
-      for (int a = 0; a < K::FM; ++a)
-#pragma unroll
-        for (int b = 0; b < K::FN; ++b) {
-          if constexpr (CF == F64)
-            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
-          else
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc[a][b], 0, 0, 0);
-        }
-    }
-    if (more) sstore(cur ^ 1);
-    __syncthreads();
-    cur ^= 1;
-  }
-}
-
-template <int CF>
-__global__ __launch_bounds__(KMajor<CF>::NT) __attribute__((amdgpu_waves_per_eu(CF == F64 ? 2 : 4))) void
-k_update_kmajor(TileView tv, int k, const GemmTask* tasks) {
-  using K = KMajor<CF>;
-  __shared__ __attribute__((aligned(16))) typename K::Buf As;
-  __shared__ __attribute__((aligned(16))) typename K::Buf Bs;
-
-  const int nb = tv.nb;
-  const int sub = nb / UBM;
-  const int lb = xcd_remap(blockIdx.x, gridDim.x);
-  const int task = lb / (sub * sub);
-  const int blk = lb % (sub * sub);
-  const int bm = blk % sub, bn = blk / sub;
-  const GemmTask t = tasks[task];
-  if (t.i == t.j && bn > bm) return;
-  if (*tv.info) return;
-
-  const void* Ap = tv.tile(t.i, k);
-  const void* Bp = tv.tile(t.j, k);
-  const int fa = tv.tfmt(t.i, k), fb = tv.tfmt(t.j, k);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave % K::WM, wn = wave / K::WM;
-  const int64_t arow0 = (int64_t)bm * UBM, brow0 = (int64_t)bn * UBM;
-
-  typename K::Acc acc[K::FM][K::FN];
-#pragma unroll
-  for (int a = 0; a < K::FM; ++a)
-#pragma unroll
-    for (int b = 0; b < K::FN; ++b) acc[a][b] = typename K::Acc{0, 0, 0, 0};
-
-  // operand tiles in any format (codes 0..4; FP8 operands carry their scale)
-  const double ma = tv.tmul(t.i, k), mb = tv.tmul(t.j, k);
-#define MPCR_PAIR(FA, FB) \
-  case FA * 5 + FB: kmajor_mainloop<CF, FA, FB>(Ap, Bp, ma, mb, nb, arow0, brow0, As, Bs, acc); break;
-#define MPCR_ROW(FA) MPCR_PAIR(FA, F64) MPCR_PAIR(FA, F32) MPCR_PAIR(FA, F16) MPCR_PAIR(FA, BF16) MPCR_PAIR(FA, F8)
-  switch (fa * 5 + fb) {
-    MPCR_ROW(F64)
-    MPCR_ROW(F32)
-    MPCR_ROW(F16)
-    MPCR_ROW(BF16)
-    MPCR_ROW(F8)
-    default: break;
-  }
-#undef MPCR_ROW
-#undef MPCR_PAIR
-
-  void* Cp = tv.tile(t.i, t.j);
-  const int fc = tv.tfmt(t.i, t.j);
-  const bool diag = (t.i == t.j);
-  auto epilogue = [&](auto fmt_tag) {
-    constexpr int FC = decltype(fmt_tag)::value;
-#pragma unroll
-    for (int a = 0; a < K::FM; ++a)
-#pragma unroll
-      for (int b = 0; b < K::FN; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int row = (CF == F64) ? ((lane >> 4) + 4 * r) : (4 * (lane >> 4) + r);
-          int64_t R = arow0 + wm * K::TM + a * 16 + row;
-          int64_t C = brow0 + wn * K::TN + b * 16 + (lane & 15);
-          if (diag && C > R) continue;
-          rmw_sub<FC>(Cp, C * nb + R, (double)acc[a][b][r]);
-        }
-  };
-  switch (fc) {
-    case F64: epilogue(std::integral_constant<int, F64>{}); break;
-    case F32: epilogue(std::integral_constant<int, F32>{}); break;
-    case F16: epilogue(std::integral_constant<int, F16>{}); break;
-    case BF16: epilogue(std::integral_constant<int, BF16>{}); break;
-    default: epilogue(std::integral_constant<int, F8>{}); break;
-  }
 }
 
 // BF16 / FP16: operands staged m-major in LDS ([m][k]) so that each lane reads
@@ -415,391 +197,6 @@ __global__ __launch_bounds__(256) void k_update_mmajor(TileView tv, int k, const
         int64_t C = brow0 + wn * 64 + b * 16 + (lane & 15);
         rmw_sub<CF>(Cp, C * nb + R, (double)acc[a][b][r]);
       }
-}
-
-// ---------------------------------------------------------------------------
-// FP32 output tiles through the BF16 MFMA.  gfx950's dense BF16 rate is 16
-// times its FP32 rate, so an FP32 product can be formed from BF16 pieces:
-// each operand, converted to FP32 as in the FP32 update, is split exactly
-// into three BF16 numbers x = h + m + l (h = bf16(x), m = bf16(x - h),
-// l = x - h - m; every difference is exact by Sterbenz's lemma and l needs at
-// most 8 significant bits), and a b is accumulated as
-//   ah bh + ah bm + am bh + ah bl + al bh + am bm
-// in FP32 on v_mfma_f32_16x16x32_bf16 (which returns the exact FP32-rounded
-// sums).  The three dropped products am bl + al bm + al bl are below
-// 2^-23 |a b|, so every update keeps FP32-level accuracy; the output tile is
-// rounded to FP32 as in the FP32 update.  One 128 x 128 block of C per
-// workgroup, 8 waves of 64 x 32, k chunks of 32; the three planes of both
-// operands (61 KB) sit in one LDS buffer so that two workgroups share a CU.
-// ---------------------------------------------------------------------------
-constexpr int SBK = 32;          // k per chunk
-constexpr int SLDK = SBK + 8;    // LDS row (halfwords): 80-byte rows put the 16 rows of a fragment read on disjoint banks
-
-__device__ __forceinline__ void split3_bf16(float x, uint16_t& h, uint16_t& m, uint16_t& l) {
-  // finite inputs: round to nearest even by adding half an ulp (ties to even)
-  uint32_t u = __float_as_uint(x);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  h = (uint16_t)(u >> 16);
-  const float r1 = x - __uint_as_float((uint32_t)h << 16);
-  uint32_t v = __float_as_uint(r1);
-  v += 0x7fffu + ((v >> 16) & 1u);
-  m = (uint16_t)(v >> 16);
-  const float r2 = r1 - __uint_as_float((uint32_t)m << 16);
-  l = (uint16_t)(__float_as_uint(r2) >> 16);  // r2 has at most 8 significant bits: exact
-}
-
-// element idx of a tile (format SF) converted to FP32 (FP8 codes scaled back
-// by mul = 2^-s)
-template <int SF>
-__device__ __forceinline__ float load1_f32(const void* p, int64_t idx, double mul) {
-  if constexpr (SF == F64) return to_f32(((const double*)p)[idx]);
-  else if constexpr (SF == F32) return ((const float*)p)[idx];
-  else if constexpr (SF == F16) return f16_to_f32(((const uint16_t*)p)[idx]);
-  else if constexpr (SF == BF16) return bf16_to_f32(((const uint16_t*)p)[idx]);
-  else return to_f32((double)e4m3_to_f32(((const uint8_t*)p)[idx]) * mul);
-}
-
-using SplitBuf = uint16_t[3][UBM][SLDK];
-
-template <int FA, int FB>
-__device__ __forceinline__ void split_mainloop(const void* Ap, const void* Bp, double ma, double mb, int nb,
-                                               int64_t arow0, int64_t brow0, SplitBuf& As, SplitBuf& Bs,
-                                               f4 (&acc)[4][2]) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  // staging: thread = one row (m) and 8 consecutive k of the chunk; a load
-  // instruction covers 64 consecutive rows of one k column (coalesced), and
-  // the split values go to LDS as one 16-byte vector per plane
-  const int mr = tid & (UBM - 1);
-  const int k0 = 8 * (tid / UBM);
-  float ra[8], rb[8];
-  auto gload = [&](int kk) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t col = kk + k0 + e;
-      ra[e] = load1_f32<FA>(Ap, col * nb + arow0 + mr, ma);
-      rb[e] = load1_f32<FB>(Bp, col * nb + brow0 + mr, mb);
-    }
-  };
-  auto sstore = [&]() {
-    u16x8 ah, am, al, bh, bm, bl;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      uint16_t h, m, l;
-      split3_bf16(ra[e], h, m, l);
-      ah[e] = h;
-      am[e] = m;
-      al[e] = l;
-      split3_bf16(rb[e], h, m, l);
-      bh[e] = h;
-      bm[e] = m;
-      bl[e] = l;
-    }
-    *(u16x8*)&As[0][mr][k0] = ah;
-    *(u16x8*)&As[1][mr][k0] = am;
-    *(u16x8*)&As[2][mr][k0] = al;
-    *(u16x8*)&Bs[0][mr][k0] = bh;
-    *(u16x8*)&Bs[1][mr][k0] = bm;
-    *(u16x8*)&Bs[2][mr][k0] = bl;
-  };
-  gload(0);
-  sstore();
-  __syncthreads();
-  const int kq8 = 8 * (lane >> 4);
-  // one LDS buffer (two workgroups per CU): the next chunk is loaded into
-  // registers during this chunk's products and stored after a barrier
-  for (int kk = 0; kk < nb; kk += SBK) {
-    const bool more = kk + SBK < nb;
-    if (more) gload(kk + SBK);
-    u16x8 a[3][4], b[3][2];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) a[p][x] = *(const u16x8*)&As[p][wm * 64 + x * 16 + (lane & 15)][kq8];
-#pragma unroll
-      for (int y = 0; y < 2; ++y) b[p][y] = *(const u16x8*)&Bs[p][wn * 32 + y * 16 + (lane & 15)][kq8];
-    }
-#define MPCR_MF(PA, PB)                                                                                   \
-  acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[PA][x]),              \
-                                                      __builtin_bit_cast(bf16x8, b[PB][y]), acc[x][y], 0, 0, 0)
-    // the small products first, the leading one last
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-        MPCR_MF(1, 1);
-        MPCR_MF(0, 2);
-        MPCR_MF(2, 0);
-        MPCR_MF(0, 1);
-        MPCR_MF(1, 0);
-        MPCR_MF(0, 0);
-      }
-#undef MPCR_MF
-    if (more) {
-      __syncthreads();
-      sstore();
-      __syncthreads();
-    }
-  }
-}
-
-__global__ __launch_bounds__(512) void k_update_f32_split(TileView tv, int k, const GemmTask* tasks) {
-  __shared__ __attribute__((aligned(16))) SplitBuf As;
-  __shared__ __attribute__((aligned(16))) SplitBuf Bs;
-
-  const int nb = tv.nb;
-  const int sub = nb / UBM;
-  const int lb = xcd_remap(blockIdx.x, gridDim.x);
-  const int task = lb / (sub * sub);
-  const int blk = lb % (sub * sub);
-  const int bm = blk % sub, bn = blk / sub;
-  const GemmTask t = tasks[task];
-  if (t.i == t.j && bn > bm) return;
-  if (*tv.info) return;
-
-  const void* Ap = tv.tile(t.i, k);
-  const void* Bp = tv.tile(t.j, k);
-  const int fa = tv.tfmt(t.i, k), fb = tv.tfmt(t.j, k);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  const int64_t arow0 = (int64_t)bm * UBM, brow0 = (int64_t)bn * UBM;
-
-  f4 acc[4][2];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = f4{0, 0, 0, 0};
-
-  const double ma = tv.tmul(t.i, k), mb = tv.tmul(t.j, k);
-#define MPCR_PAIR(FA, FB) \
-  case FA * 5 + FB: split_mainloop<FA, FB>(Ap, Bp, ma, mb, nb, arow0, brow0, As, Bs, acc); break;
-#define MPCR_ROW(FA) MPCR_PAIR(FA, F64) MPCR_PAIR(FA, F32) MPCR_PAIR(FA, F16) MPCR_PAIR(FA, BF16) MPCR_PAIR(FA, F8)
-  switch (fa * 5 + fb) {
-    MPCR_ROW(F64)
-    MPCR_ROW(F32)
-    MPCR_ROW(F16)
-    MPCR_ROW(BF16)
-    MPCR_ROW(F8)
-    default: break;
-  }
-#undef MPCR_ROW
-#undef MPCR_PAIR
-
-  void* Cp = tv.tile(t.i, t.j);  // FP32 (the update runs in the output tile's format)
-  const bool diag = (t.i == t.j);
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t R = arow0 + wm * 64 + x * 16 + 4 * (lane >> 4) + r;
-        const int64_t C = brow0 + wn * 32 + y * 16 + (lane & 15);
-        if (diag && C > R) continue;
-        rmw_sub<F32>(Cp, C * nb + R, (double)acc[x][y][r]);
-      }
-}
-
-// Split panels: after the TRSM of step k, every panel tile (i, k) is converted
-// to FP32 and split once into its three BF16 planes, stored for the update
-// kernel in chunks of 32 k: plane p of panel tile q = i - k - 1 at
-//   out3[(q * 3 + p) * nb^2 + (c * nb + row) * 32 + kk]   (k = 32 c + kk),
-// so a 128-row block of one chunk is 8 contiguous KB.  The FP32 updates of the
-// step then copy planes instead of splitting every operand in every block.
-// outb (when not NULL) receives, in the same layout, each element rounded once
-// to BF16 from its stored format: the operands of the step's BF16 updates.
-template <int SF>
-__device__ __forceinline__ uint16_t load1_bf16(const void* p, int64_t idx, double mul) {
-  if constexpr (SF == BF16) return ((const uint16_t*)p)[idx];
-  else if constexpr (SF == F32) return f32_to_bf16_rne(((const float*)p)[idx]);
-  else if constexpr (SF == F64) return to_bf16(((const double*)p)[idx]);
-  else if constexpr (SF == F16) return to_bf16((double)f16_to_f32(((const uint16_t*)p)[idx]));
-  else return to_bf16((double)e4m3_to_f32(((const uint8_t*)p)[idx]) * mul);
-}
-
-__global__ __launch_bounds__(512) void k_pack_split(TileView tv, int k, uint16_t* out3, uint16_t* outb) {
-  const int nb = tv.nb, nch = nb / SBK, nrb = nb / UBM;
-  const int b = blockIdx.x;
-  const int q = b / (nch * nrb), c = (b / nrb) % nch, rb = b % nrb;
-  const int i = k + 1 + q;
-  const void* P = tv.tile(i, k);
-  const int f = tv.tfmt(i, k);
-  const double mul = tv.tmul(i, k);
-  const int mr = threadIdx.x & (UBM - 1), k0 = 8 * (threadIdx.x / UBM);
-  const int64_t row = (int64_t)rb * UBM + mr;
-  const int64_t nb2 = (int64_t)nb * nb;
-  const int64_t at = ((int64_t)c * nb + row) * SBK + k0;
-  float v[8];
-  u16x8 bv;
-  auto load = [&](auto tag) {
-    constexpr int SF = decltype(tag)::value;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t idx = (int64_t)(SBK * c + k0 + e) * nb + row;
-      if (out3) v[e] = load1_f32<SF>(P, idx, mul);
-      if (outb) bv[e] = load1_bf16<SF>(P, idx, mul);
-    }
-  };
-  switch (f) {
-    case F64: load(std::integral_constant<int, F64>{}); break;
-    case F32: load(std::integral_constant<int, F32>{}); break;
-    case F16: load(std::integral_constant<int, F16>{}); break;
-    case BF16: load(std::integral_constant<int, BF16>{}); break;
-    default: load(std::integral_constant<int, F8>{}); break;
-  }
-  if (outb) *(u16x8*)(outb + (int64_t)q * nb2 + at) = bv;
-  if (out3) {
-    u16x8 h, m, l;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      uint16_t a, bb, cc;
-      split3_bf16(v[e], a, bb, cc);
-      h[e] = a;
-      m[e] = bb;
-      l[e] = cc;
-    }
-    uint16_t* o = out3 + (int64_t)q * 3 * nb2 + at;
-    *(u16x8*)o = h;
-    *(u16x8*)(o + nb2) = m;
-    *(u16x8*)(o + 2 * nb2) = l;
-  }
-}
-
-hipError_t launch_pack_split(const TileView& tv, int k, uint16_t* out3, uint16_t* outb, hipStream_t s) {
-  const int cnt = tv.nt - k - 1;
-  if (cnt <= 0 || (!out3 && !outb)) return hipSuccess;
-  k_pack_split<<<cnt * (tv.nb / SBK) * (tv.nb / UBM), 512, 0, s>>>(tv, k, out3, outb);
-  return hipGetLastError();
-}
-
-// Updates from the packed panels of step k (see k_pack_split), planes copied
-// with 16-byte loads (four per row of a chunk).  NPL = 3: FP32 output tiles,
-// the six split products of k_update_f32_split; NPL = 1: BF16 output tiles,
-// one BF16 product per fragment pair on operands rounded once to BF16 (the
-// same k order of MFMAs as k_update_mmajor<BF16>, so the same results).  NW waves per 128 x 128 block: 8 waves of 64 x 32 or
-// 4 waves of 64 x 64; both run at the same rate in the factorisation (about
-// 112 TF/s FP32-equivalent at n = 32768), where the three planes (6 bytes per
-// operand element) make the operand stream, not the LDS or the MFMA, the limit.
-constexpr int SPLIT_WAVES = 8;
-
-template <int NW, int NPL>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 8 ? 4 : 2))) void
-k_update_packed(TileView tv, int k, const GemmTask* tasks, const uint16_t* split) {
-  constexpr int NT = 64 * NW;
-  constexpr int WN = NW / 2;             // waves along n (2 along m)
-  constexpr int FY = (UBM / WN) / 16;    // 16-column MFMA tiles per wave along n
-  constexpr int G = NPL * UBM * 4 / NT;  // 16-byte vectors per thread per operand and chunk
-  constexpr int CF = NPL == 3 ? F32 : BF16;
-  __shared__ __attribute__((aligned(16))) uint16_t As[NPL][UBM][SLDK];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[NPL][UBM][SLDK];
-
-  const int nb = tv.nb;
-  const int sub = nb / UBM;
-  const int lb = xcd_remap(blockIdx.x, gridDim.x);
-  const int task = lb / (sub * sub);
-  const int blk = lb % (sub * sub);
-  const int bm = blk % sub, bn = blk / sub;
-  const GemmTask t = tasks[task];
-  if (t.i == t.j && bn > bm) return;
-  if (*tv.info) return;
-
-  const int64_t nb2 = (int64_t)nb * nb;
-  const uint16_t* Ap = split + (int64_t)(t.i - k - 1) * NPL * nb2;
-  const uint16_t* Bp = split + (int64_t)(t.j - k - 1) * NPL * nb2;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  const int64_t arow0 = (int64_t)bm * UBM, brow0 = (int64_t)bn * UBM;
-
-  f4 acc[4][FY];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < FY; ++y) acc[x][y] = f4{0, 0, 0, 0};
-
-  // vector v = tid + NT g: plane v / 512, row (v % 512) / 4, k offset 8 (v % 4)
-  u16x8 ra[G], rb[G];
-  auto gload = [&](int kk) {
-    const int64_t c = kk / SBK;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int v = tid + NT * g, p = v / (UBM * 4), r = (v % (UBM * 4)) >> 2, k0 = 8 * (v & 3);
-      ra[g] = *(const u16x8*)(Ap + p * nb2 + (c * nb + arow0 + r) * SBK + k0);
-      rb[g] = *(const u16x8*)(Bp + p * nb2 + (c * nb + brow0 + r) * SBK + k0);
-    }
-  };
-  auto sstore = [&]() {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int v = tid + NT * g, p = v / (UBM * 4), r = (v % (UBM * 4)) >> 2, k0 = 8 * (v & 3);
-      *(u16x8*)&As[p][r][k0] = ra[g];
-      *(u16x8*)&Bs[p][r][k0] = rb[g];
-    }
-  };
-  gload(0);
-  sstore();
-  __syncthreads();
-  const int kq8 = 8 * (lane >> 4);
-  for (int kk = 0; kk < nb; kk += SBK) {
-    const bool more = kk + SBK < nb;
-    if (more) gload(kk + SBK);
-    u16x8 a[NPL][4], b[NPL][FY];
-#pragma unroll
-    for (int p = 0; p < NPL; ++p) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) a[p][x] = *(const u16x8*)&As[p][wm * 64 + x * 16 + (lane & 15)][kq8];
-#pragma unroll
-      for (int y = 0; y < FY; ++y) b[p][y] = *(const u16x8*)&Bs[p][wn * (16 * FY) + y * 16 + (lane & 15)][kq8];
-    }
-#define MPCR_MF(PA, PB)                                                                                   \
-  acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[PA][x]),              \
-                                                      __builtin_bit_cast(bf16x8, b[PB][y]), acc[x][y], 0, 0, 0)
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-      for (int y = 0; y < FY; ++y) {
-        if constexpr (NPL == 3) {
-          MPCR_MF(1, 1);
-          MPCR_MF(0, 2);
-          MPCR_MF(2, 0);
-          MPCR_MF(0, 1);
-          MPCR_MF(1, 0);
-        }
-        MPCR_MF(0, 0);
-      }
-#undef MPCR_MF
-    if (more) {
-      __syncthreads();
-      sstore();
-      __syncthreads();
-    }
-  }
-
-  void* Cp = tv.tile(t.i, t.j);
-  const bool diag = (t.i == t.j);
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < FY; ++y)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t R = arow0 + wm * 64 + x * 16 + 4 * (lane >> 4) + r;
-        const int64_t C = brow0 + wn * (16 * FY) + y * 16 + (lane & 15);
-        if (diag && C > R) continue;
-        rmw_sub<CF>(Cp, C * nb + R, (double)acc[x][y][r]);
-      }
-}
-
-hipError_t launch_tile_update_packed(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks,
-                                     const uint16_t* planes, hipStream_t s) {
-  if (ntasks == 0) return hipSuccess;
-  const int sub = tv.nb / UBM;
-  if (cfmt == F32)
-    k_update_packed<SPLIT_WAVES, 3><<<ntasks * sub * sub, 64 * SPLIT_WAVES, 0, s>>>(tv, k, tasks, planes);
-  else if (cfmt == BF16)
-    k_update_packed<8, 1><<<ntasks * sub * sub, 512, 0, s>>>(tv, k, tasks, planes);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -996,6 +393,15 @@ hipError_t launch_tile_update_fp8(const TileView& tv, int k, const GemmTask* tas
   return hipGetLastError();
 }
 
+// 16-bit output tiles
+hipError_t launch_tile_update_16(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks, hipStream_t s) {
+  const int sub = tv.nb / UBM;
+  if (cfmt == BF16) k_update_mmajor<BF16><<<ntasks * sub * sub, 256, 0, s>>>(tv, k, tasks);
+  else if (cfmt == F16) k_update_mmajor<F16><<<ntasks * sub * sub, 256, 0, s>>>(tv, k, tasks);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 // largest magnitude of each panel tile (i, k), i > k (widened values)
 __global__ __launch_bounds__(256) void k_panel_amax(TileView tv, int k, double* pamax) {
   const int i = k + 1 + blockIdx.x;
@@ -1018,26 +424,6 @@ hipError_t launch_panel_amax(const TileView& tv, int k, double* pamax, hipStream
   const int cnt = tv.nt - k - 1;
   if (cnt <= 0) return hipSuccess;
   k_panel_amax<<<cnt, 256, 0, s>>>(tv, k, pamax);
-  return hipGetLastError();
-}
-
-hipError_t launch_tile_update(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks,
-                              hipStream_t s, bool fp32_split) {
-  if (ntasks == 0) return hipSuccess;
-  const int sub = tv.nb / UBM;
-  dim3 grid(ntasks * sub * sub);
-  switch (cfmt) {
-    case F64: k_update_kmajor<F64><<<grid, KMajor<F64>::NT, 0, s>>>(tv, k, tasks); break;
-    case F32:
-      if (fp32_split)
-        k_update_f32_split<<<grid, 512, 0, s>>>(tv, k, tasks);
-      else
-        k_update_kmajor<F32><<<grid, KMajor<F32>::NT, 0, s>>>(tv, k, tasks);
-      break;
-    case BF16: k_update_mmajor<BF16><<<grid, 256, 0, s>>>(tv, k, tasks); break;
-    case F16: k_update_mmajor<F16><<<grid, 256, 0, s>>>(tv, k, tasks); break;
-    default: return hipErrorInvalidValue;
-  }
   return hipGetLastError();
 }
 

@@ -177,6 +177,30 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
   return xcd * per + (xcd < rem ? xcd : rem) + idx;
 }
 
+// Direct global-to-LDS copy: every lane's 16 bytes at base + off go to LDS byte
+// address l + 16 lane.  base and l are wave-uniform.  The copy is asynchronous
+// (vmcnt) and unknown to the compiler: wait_vmcnt before the barrier that hands
+// the data to the readers.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+__device__ __forceinline__ void copy16_to_lds(const void* base, uint32_t off, uint32_t l) {
+  uint32_t m0;  // (kept for the compiler, which does not see the register change)
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %3\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %2\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(m0)
+      : "v"(off), "s"(base), "s"(l)
+      : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%c0)" : : "n"(N) : "memory");
+}
+
 struct GemmTask {
   int i, j;  // output tile (i, j); operands are tiles (i, k) and (j, k)
 };
@@ -258,10 +282,8 @@ hipError_t launch_pack_split(const TileView& tv, int k, uint16_t* out3, uint16_t
 // products) or BF16 (one plane)
 hipError_t launch_tile_update_packed(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks,
                                      const uint16_t* planes, hipStream_t s);
-// fp32_split: FP32 output tiles through the BF16 MFMA with operands split
-// into three BF16 parts (FP32-level accuracy); else the FP32 MFMA
-hipError_t launch_tile_update(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks,
-                              hipStream_t s, bool fp32_split = false);
+hipError_t launch_tile_update(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks, hipStream_t s);
+hipError_t launch_tile_update_16(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks, hipStream_t s);
 hipError_t launch_logdet(const TileView& tv, double* out, hipStream_t s);
 hipError_t launch_trtri_diag(const TileView& tv, double* Linv, const double* dinv, hipStream_t s);
 
