@@ -658,9 +658,6 @@ struct SigmaOp {
     };
     return ctx ? timed(ctx, s, 9, 2.0 * (double)n * n * nrhs, go) : go();
   }
-  hipError_t rowsum(double* out, hipStream_t s) const {
-    return A ? launch_rowsum_abs_dense(n, A, lda, out, s) : launch_rowsum_abs_cov(n, locs, th, out, s);
-  }
 };
 
 // Solver options common to mpcr_potrs and mpcr_gauss_loglik.

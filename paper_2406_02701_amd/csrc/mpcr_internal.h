@@ -310,10 +310,6 @@ hipError_t launch_residual_dense(int n, const double* A, int64_t lda, const doub
 size_t residual_part_bytes(int nb, int nt);
 hipError_t launch_residual_tiles(int n, int nb, int nt, const double* sig64, const double* B, const double* X,
                                  double* R, int64_t ld, int nrhs, hipStream_t s, double* rowsum, double* part);
-hipError_t launch_rowsum_abs_cov(int n, const double* locs, const mpcr_theta_t& th, double* out,
-                                 hipStream_t s);
-hipError_t launch_rowsum_abs_dense(int n, const double* A, int64_t lda, double* out, hipStream_t s);
-
 // column reductions over the first n rows of n x nrhs blocks (ld), deterministic
 hipError_t launch_col_dot(int n, int nrhs, const double* A, const double* B, int64_t ld, double* partial,
                           double* out, hipStream_t s);

@@ -397,112 +397,125 @@ __device__ __forceinline__ double matern_corr_s(double x, int nuc) {
 
 static int nu_code_s(double nu) { return nu == 0.5 ? 0 : (nu == 1.5 ? 1 : 2); }
 
-// One workgroup per 64 rows; thread (r, q) sums columns q, q+4, ... of each
-// 256-column chunk; the four partials are combined in a fixed order.
-// MODE 0: R = B - Sigma X (B == NULL: R = -Sigma X) ; MODE 1: R[:,0] = sum_c |Sigma_rc|.
-// DENSE: Sigma read from the FP64 matrix A instead of regenerated from the sites.
-template <int MODE, bool DENSE>
-__global__ __launch_bounds__(256) void k_sigma_apply(int n, const double* locs, double s2, double range, int nuc,
-                                                     double nugget, const double* A, int64_t lda, const double* B,
-                                                     const double* X, double* R, int64_t ld, int nrhs,
-                                                     double* rowsum) {
-  constexpr int CC = 256;
-  __shared__ double Ls[2][CC];
-  __shared__ double Xs[CC * RHS_CHUNK];
-  __shared__ double part[4][64][RHS_CHUNK + 1];  // [.][.][RHS_CHUNK]: |Sigma| row sums
-  const int tid = threadIdx.x, r = tid & 63, q = tid >> 6;
-  const int row = blockIdx.x * 64 + r;
+// R = B - Sigma X (B == NULL: R = -Sigma X) for 16 rows per workgroup and up to
+// 16 NCH right-hand sides per pass, as an FP64 MFMA contraction whose A operand
+// is made on the spot: Sigma's entry from the sites, or (DENSE) read from the
+// FP64 matrix A.  Wave w takes the 16-column groups w, w + W, ... of Sigma; in
+// a group, lane (q = l / 16, r = l % 16) supplies row r at the columns
+// 4 q .. 4 q + 3 (one per MFMA) and column r of X at the same four rows.  The
+// waves' partial products (and with rowsum their sums of |Sigma_rc|) are added
+// in wave order, so the result does not depend on scheduling.
+// Bound: from the sites, by the FP64 exp, sqrt and divide of every entry (about
+// 120 instructions); dense, by reading A.  One entry per lane and 16 rows per
+// workgroup fill the chip from n of a few hundred on; a version with one row
+// per thread and 64 rows per workgroup ran 16 of 256 CUs at n = 1000, and did 16
+// right-hand sides' work for one.  Measured, before -> after: sites, n = 1000,
+// one column 92 -> 17 us; sites, n = 7919, one column 757 -> 243 us; dense, n = 4000,
+// 32 columns 728 -> 69 us.
+template <bool DENSE, int NCH, int W>
+__global__ __launch_bounds__(64 * W) void k_sigma_apply(int n, const double* locs, double s2, double range, int nuc,
+                                                        double nugget, const double* A, int64_t lda, const double* B,
+                                                        const double* X, double* R, int64_t ld, int nrhs,
+                                                        double* rowsum) {
+  __shared__ double red[W][16][16 * NCH + 1];
+  __shared__ double rs[W][16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, r = lane & 15;
+  const int row = blockIdx.x * 16 + r;
   const bool live = row < n;
-  double px = 0, py = 0;
-  if (!DENSE && live) { px = locs[row]; py = locs[n + row]; }
-  const int ncol = MODE == 1 ? 1 : nrhs;
-  for (int c0 = 0; c0 < ncol; c0 += RHS_CHUNK) {
-    double acc[RHS_CHUNK];
-    double asum = 0.0;  // sum_c |Sigma_rc| when rowsum is requested (first chunk only)
+  const double px = !DENSE && live ? locs[row] : 0.0, py = !DENSE && live ? locs[n + row] : 0.0;
+  for (int c0 = 0; c0 < nrhs; c0 += 16 * NCH) {
+    d4 acc[NCH];
 #pragma unroll
-    for (int j = 0; j < RHS_CHUNK; ++j) acc[j] = 0.0;
-    for (int k0 = 0; k0 < n; k0 += CC) {
-      __syncthreads();
-      for (int e = tid; e < CC; e += 256) {
-        int c = k0 + e;
-        if (!DENSE) {
-          Ls[0][e] = c < n ? locs[c] : 0.0;
-          Ls[1][e] = c < n ? locs[n + c] : 0.0;
+    for (int h = 0; h < NCH; ++h) acc[h] = d4{0, 0, 0, 0};
+    double asum = 0.0;
+    const double* Xc[NCH];
+#pragma unroll
+    for (int h = 0; h < NCH; ++h) Xc[h] = c0 + 16 * h + r < nrhs ? X + (int64_t)(c0 + 16 * h + r) * ld : nullptr;
+    for (int k0 = 16 * w; k0 < n; k0 += 16 * W) {
+      double sv[4], xv[NCH][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int col = k0 + 4 * q + u;
+        const bool in = col < n;
+#pragma unroll
+        for (int h = 0; h < NCH; ++h) xv[h][u] = in && Xc[h] ? Xc[h][col] : 0.0;
+        if (DENSE) {
+          sv[u] = in && live ? A[(int64_t)col * lda + row] : 0.0;
+        } else {
+          const double dx = px - (in ? locs[col] : 0.0), dy = py - (in ? locs[n + col] : 0.0);
+          double v = s2 * matern_corr_s(sqrt(dx * dx + dy * dy) / range, nuc);
+          if (col == row) v += nugget;
+          sv[u] = in && live ? v : 0.0;
         }
       }
-      if (MODE == 0)
-        for (int e = tid; e < CC * RHS_CHUNK; e += 256) {
-          int kk = e % CC, j = e / CC;
-          Xs[kk * RHS_CHUNK + j] = (k0 + kk < n && c0 + j < nrhs) ? X[(int64_t)(c0 + j) * ld + k0 + kk] : 0.0;
-        }
-      __syncthreads();
-      if (live) {
-        const int kend = (n - k0) < CC ? (n - k0) : CC;
-        for (int kk = q; kk < kend; kk += 4) {
-          const int col = k0 + kk;
-          double sv;
-          if (DENSE) {
-            sv = A[(int64_t)col * lda + row];
-          } else {
-            double dx = px - Ls[0][kk], dy = py - Ls[1][kk];
-            sv = s2 * matern_corr_s(sqrt(dx * dx + dy * dy) / range, nuc);
-            if (col == row) sv += nugget;
-          }
-          if (MODE == 1) {
-            acc[0] += fabs(sv);
-          } else {
-            asum += fabs(sv);
 #pragma unroll
-            for (int j = 0; j < RHS_CHUNK; ++j) acc[j] += sv * Xs[kk * RHS_CHUNK + j];
-          }
-        }
+      for (int u = 0; u < 4; ++u) {
+        asum += fabs(sv[u]);
+#pragma unroll
+        for (int h = 0; h < NCH; ++h) acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(sv[u], xv[h][u], acc[h], 0, 0, 0);
       }
     }
-    __syncthreads();
+    const bool sums = rowsum && c0 == 0;
+    if (sums) {
+      asum += __shfl_xor(asum, 16);
+      asum += __shfl_xor(asum, 32);
+      if (lane < 16) rs[w][lane] = asum;
+    }
 #pragma unroll
-    for (int j = 0; j < RHS_CHUNK; ++j) part[q][r][j] = acc[j];
-    part[q][r][RHS_CHUNK] = asum;
+    for (int h = 0; h < NCH; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[w][q + 4 * e][16 * h + r] = acc[h][e];
     __syncthreads();
-    if (MODE == 0 && rowsum && c0 == 0 && tid < 64 && blockIdx.x * 64 + tid < n)
-      rowsum[blockIdx.x * 64 + tid] = ((part[0][tid][RHS_CHUNK] + part[1][tid][RHS_CHUNK]) + part[2][tid][RHS_CHUNK]) +
-                                      part[3][tid][RHS_CHUNK];
-    for (int e = tid; e < 64 * RHS_CHUNK; e += 256) {
-      int rr = e % 64, j = e / 64;
-      int grow = blockIdx.x * 64 + rr, c = c0 + j;
-      if (grow < n && c < ncol) {
-        double s = ((part[0][rr][j] + part[1][rr][j]) + part[2][rr][j]) + part[3][rr][j];
-        if (MODE == 1)
-          R[grow] = s;
-        else
-          R[(int64_t)c * ld + grow] = (B ? B[(int64_t)c * ld + grow] : 0.0) - s;
+    for (int e = tid; e < 256 * NCH; e += 64 * W) {
+      const int rr = e % 16, cc = e / 16, grow = blockIdx.x * 16 + rr, c = c0 + cc;
+      if (grow < n && c < nrhs) {
+        double s = red[0][rr][cc];
+#pragma unroll
+        for (int x = 1; x < W; ++x) s += red[x][rr][cc];
+        R[(int64_t)c * ld + grow] = (B ? B[(int64_t)c * ld + grow] : 0.0) - s;
       }
     }
+    if (sums && tid < 16 && blockIdx.x * 16 + tid < n) {
+      double s = rs[0][tid];
+#pragma unroll
+      for (int x = 1; x < W; ++x) s += rs[x][tid];
+      rowsum[blockIdx.x * 16 + tid] = s;
+    }
+    __syncthreads();
   }
+}
+
+// Sixteen waves per workgroup while the 16-row groups leave CUs without one
+// (n = 4096 is one group per CU), else eight; as many 16-column chunks per pass
+// as there are right-hand sides, up to four (an entry of Sigma is made once a pass).
+template <bool DENSE>
+static void sigma_apply(int n, const double* locs, const mpcr_theta_t& th, const double* A, int64_t lda,
+                        const double* B, const double* X, double* R, int64_t ld, int nrhs, double* rowsum,
+                        hipStream_t s) {
+#define MPCR_SIGMA(NCH, W)                                                                                          \
+  k_sigma_apply<DENSE, NCH, W><<<(n + 15) / 16, 64 * W, 0, s>>>(n, locs, th.sigma2, th.range, nu_code_s(th.nu),     \
+                                                               th.nugget, A, lda, B, X, R, ld, nrhs, rowsum)
+  if (n <= 4096) {
+    if (nrhs <= 16) MPCR_SIGMA(1, 16);
+    else MPCR_SIGMA(2, 16);
+  } else {
+    if (nrhs <= 16) MPCR_SIGMA(1, 8);
+    else if (nrhs <= 32) MPCR_SIGMA(2, 8);
+    else MPCR_SIGMA(4, 8);
+  }
+#undef MPCR_SIGMA
 }
 
 hipError_t launch_residual_cov(int n, const double* locs, const mpcr_theta_t& th, const double* B, const double* X,
                                double* R, int64_t ld, int nrhs, hipStream_t s, double* rowsum) {
   if (n == 0) return hipSuccess;
-  k_sigma_apply<0, false><<<(n + 63) / 64, 256, 0, s>>>(n, locs, th.sigma2, th.range, nu_code_s(th.nu), th.nugget,
-                                                        nullptr, 0, B, X, R, ld, nrhs, rowsum);
+  sigma_apply<false>(n, locs, th, nullptr, 0, B, X, R, ld, nrhs, rowsum, s);
   return hipGetLastError();
 }
 hipError_t launch_residual_dense(int n, const double* A, int64_t lda, const double* B, const double* X, double* R,
                                  int64_t ld, int nrhs, hipStream_t s, double* rowsum) {
   if (n == 0) return hipSuccess;
-  k_sigma_apply<0, true><<<(n + 63) / 64, 256, 0, s>>>(n, nullptr, 0, 1, 0, 0, A, lda, B, X, R, ld, nrhs, rowsum);
-  return hipGetLastError();
-}
-hipError_t launch_rowsum_abs_cov(int n, const double* locs, const mpcr_theta_t& th, double* out, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_sigma_apply<1, false><<<(n + 63) / 64, 256, 0, s>>>(n, locs, th.sigma2, th.range, nu_code_s(th.nu), th.nugget,
-                                                        nullptr, 0, nullptr, nullptr, out, 0, 1, nullptr);
-  return hipGetLastError();
-}
-hipError_t launch_rowsum_abs_dense(int n, const double* A, int64_t lda, double* out, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  k_sigma_apply<1, true><<<(n + 63) / 64, 256, 0, s>>>(n, nullptr, 0, 1, 0, 0, A, lda, nullptr, nullptr, out, 0, 1,
-                                                       nullptr);
+  sigma_apply<true>(n, nullptr, mpcr_theta_t{0, 1, 0.5, 0}, A, lda, B, X, R, ld, nrhs, rowsum, s);
   return hipGetLastError();
 }
 
