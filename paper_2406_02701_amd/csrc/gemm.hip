@@ -3,17 +3,15 @@
 // The paper's section "Linear Algebra Functions Performance" multiplies the
 // same matrices in double, single and half precision; here each input format
 // has its own MFMA path on gfx950:
-//   FP64  v_mfma_f64_16x16x4f64      (FP64 accumulation)
-//   FP32  v_mfma_f32_16x16x4f32      (FP32 accumulation)
-//   BF16  v_mfma_f32_16x16x32_bf16   (FP32 accumulation)
-//   FP16  v_mfma_f32_16x16x32_f16    (FP32 accumulation)
-//   FP8   v_mfma_f32_16x16x32_fp8_fp8 (FP32 accumulation); each 128-wide k block
-//         is accumulated separately and added with its factor 2^-(sA + sB)
-// One workgroup computes a 128 x 128 block of C with four waves (2 x 2), each
-// 64 x 64 = 4 x 4 MFMA tiles; operands are staged through LDS, k-major for the
-// FP64/FP32 paths and row-major (k contiguous per row) for the 16/8-bit paths.
-// The FP8 k blocks of 128 are those of the block scaling (one exponent per
-// 128 x 128 block of each operand).
+//   FP64  v_mfma_f64_16x16x4f64                 (FP64 accumulation)
+//   FP32  v_mfma_f32_16x16x4f32                 (FP32 accumulation)
+//   BF16  v_mfma_f32_16x16x32_bf16              (FP32 accumulation)
+//   FP16  v_mfma_f32_16x16x32_f16               (FP32 accumulation)
+//   FP8   v_mfma_scale_f32_16x16x128_f8f6f4     (FP32 accumulation), the block
+//         exponents as the instruction's scales
+// Operands are staged through LDS, k-major for FP64/FP32 and row-major (k
+// contiguous per row) for the 16/8-bit formats.  The FP8 k blocks of 128 are
+// those of the block scaling (one exponent per 128 x 128 block of each operand).
 #include <type_traits>
 
 #include "mpcr_internal.h"
@@ -26,30 +24,122 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int GB = 128;  // block of C per workgroup
-
-// FP64 uses 8 waves of 64 x 32 (more waves per CU hide the staging of the
-// slow FP64 MFMA better than more work per wave), FP32 4 waves of 64 x 64;
-// both stage 16 k per chunk, double-buffered with one barrier per chunk (the
-// shapes of the factorisation's tile-update loop).
+// FP64 / FP32 path: blocks of (16 FM WM) x (16 FN WN) of C by WM x WN waves of
+// FM x FN MFMA tiles; both operands are staged k-major through LDS, 16 k per
+// chunk, double-buffered with one barrier per chunk, the next chunk's loads in
+// flight during the current one's MFMAs.
+//   Loads are 16-byte vectors along the stored columns at the elements' own
+// alignment, whatever the sizes and leading dimensions: a vector that crosses
+// the last row or column is read element by element with clamped indexes (what
+// lies past the edge only feeds results that are not stored), and only a last
+// chunk of fewer than 16 k takes a checked path, which fills up with zeros.
+//   A transposed operand's vector is four (FP64: two) k of one row and is
+// scattered to as many LDS rows; the row index is exclusive-or'ed with 16
+// (FP64: 4) times the k group, which puts a wave's 64 stores on 64 different
+// banks and leaves the fragment reads, which stay inside a group (FP64: inside
+// 16 rows), free of conflicts.
+//   FP64 takes the B fragment first, so that a store instruction writes 16
+// consecutive rows; FP32 stores a lane's four consecutive rows as one vector.
+// Bound by the matrix cores (133 of 157 TF/s FP32, 62 of 79 FP64 at 8192^3) once
+// the blocks fill the chip.  Measured, whole call, against 128 x 128 blocks that
+// took a ragged size or k element by element: FP32 NT 3000^3 1370 -> 541 us, NN
+// 8192^3 10.1 -> 8.3 ms, TN 1000^3 243 -> 49 us; FP64 NT 3000^3 1513 -> 1035 us,
+// NN 8192^3 22.0 -> 17.7 ms.
 template <int P> struct GTraits;
-template <> struct GTraits<F64> { using S = double; static constexpr int BK = 16, NW = 8, WPE = 2; };
-template <> struct GTraits<F32> { using S = float; static constexpr int BK = 16, NW = 4, WPE = 2; };
+template <> struct GTraits<F64> {
+  using S = double;
+  using Acc = d4;
+  typedef double Vec __attribute__((ext_vector_type(2), aligned(8)));
+};
+template <> struct GTraits<F32> {
+  using S = float;
+  using Acc = f4;
+  typedef float Vec __attribute__((ext_vector_type(4), aligned(4)));
+};
+constexpr int GPAD = 16;  // rows k, k+1 (FP64) or k .. k+3 (FP32) of a fragment on disjoint banks
 
-// FP64 / FP32 path: operands staged k-major ([BK][GB + pad]) through LDS.
-template <int P>
-__global__ __launch_bounds__(GTraits<P>::NW * 64) __attribute__((amdgpu_waves_per_eu(GTraits<P>::WPE))) void
-k_gemm(int transA, int transB, int64_t M, int64_t N, int64_t K, double alpha, const void* Av, int64_t lda,
-       const void* Bv, int64_t ldb, double beta, void* Cv, int64_t ldc, int cprec) {
+// One operand's way into LDS.  TR: the stored matrix is k x rows (a row's k are
+// contiguous), else rows x k.
+template <int P, int NT, int BR, int BK, bool TR>
+struct GOperand {
   using S = typename GTraits<P>::S;
-  constexpr int BK = GTraits<P>::BK, NW = GTraits<P>::NW, NT = NW * 64;
-  constexpr int WM = 2, WN = NW / WM, TM = GB / WM, TN = GB / WN, FM = TM / 16, FN = TN / 16;
-  constexpr int PADK = 16;  // rows k, k+1 (FP64) or k .. k+3 (FP32) of a fragment on disjoint banks
-  __shared__ __attribute__((aligned(16))) S As[2][BK][GB + PADK];
-  __shared__ __attribute__((aligned(16))) S Bs[2][BK][GB + PADK];
+  using Vec = typename GTraits<P>::Vec;
+  static constexpr int V = 16 / sizeof(S), NV = BR * BK / V / NT, LD = BR + GPAD;
+  static_assert(NV * NT * V == BR * BK, "whole vectors per thread");
+  const S* p[NV];  // each vector's first element in chunk 0 (row clamped)
+  int64_t step;    // elements from one chunk to the next
+  bool cross[NV];  // (not TR) the vector crosses the last row
+  int last[NV];    // ... the offset of the last row's element
+  Vec v[NV];
 
-  const S* A = (const S*)Av;
-  const S* B = (const S*)Bv;
+  static __device__ __forceinline__ int row(int e) { return TR ? e / (BK / V) : (e % (BR / V)) * V; }
+  static __device__ __forceinline__ int kk(int e) { return TR ? (e % (BK / V)) * V : e / (BR / V); }
+  // LDS column of row r, k
+  static __device__ __forceinline__ int col(int r, int k) {
+    constexpr int SPREAD = (P == F64 ? 32 : 64) / (BK / V);
+    return TR ? r ^ (SPREAD * (k / V)) : r;
+  }
+  __device__ __forceinline__ void init(const S* A, int64_t ld, int64_t r0, int64_t rows, int tid) {
+    step = TR ? BK : BK * ld;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = tid + NT * i;
+      const int64_t r = r0 + row(e), rc = r < rows ? r : rows - 1;
+      p[i] = TR ? A + rc * ld + kk(e) : A + rc + kk(e) * ld;
+      cross[i] = !TR && rc + V > rows;
+      last[i] = (int)(rows - 1 - rc < V ? rows - 1 - rc : V);
+    }
+  }
+  __device__ __forceinline__ void load() {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      if (!cross[i]) {
+        v[i] = *(const Vec*)p[i];
+      } else {
+#pragma unroll
+        for (int u = 0; u < V; ++u) v[i][u] = p[i][u < last[i] ? u : last[i]];
+      }
+      p[i] += step;
+    }
+  }
+  __device__ __forceinline__ void load_tail(int left, int tid) {  // left < BK k
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int k = kk(tid + NT * i);
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        const int o = TR ? u : (u < last[i] ? u : last[i]);
+        v[i][u] = (TR ? k + u : k) < left ? p[i][o] : (S)0;
+      }
+    }
+  }
+  __device__ __forceinline__ void store(S (*lds)[LD], int tid) const {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int e = tid + NT * i, r = row(e), k = kk(e);
+      if constexpr (TR) {
+#pragma unroll
+        for (int u = 0; u < V; ++u) lds[k + u][col(r, k)] = v[i][u];
+      } else {
+        typedef S VecA __attribute__((ext_vector_type(16 / sizeof(S))));
+        *(VecA*)&lds[k][r] = (VecA)v[i];
+      }
+    }
+  }
+};
+
+template <int P, int WM, int WN, int FM, int FN, int BK, bool TA, bool TB>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void
+k_gemm(int64_t M, int64_t N, int64_t K, double alpha, const void* Av, int64_t lda, const void* Bv, int64_t ldb,
+       double beta, void* Cv, int64_t ldc, int cprec) {
+  using S = typename GTraits<P>::S;
+  using Acc = typename GTraits<P>::Acc;
+  constexpr int NT = 64 * WM * WN, BM = 16 * FM * WM, BN = 16 * FN * WN;
+  using OpA = GOperand<P, NT, BM, BK, TA>;
+  using OpB = GOperand<P, NT, BN, BK, !TB>;
+  __shared__ __attribute__((aligned(16))) S As[2][BK][OpA::LD];
+  __shared__ __attribute__((aligned(16))) S Bs[2][BK][OpB::LD];
+
   // XCD-aware order: each XCD sweeps a contiguous run of blocks, grouped 8 block
   // rows high so that the blocks in flight on one XCD share A and B panels
   const int gm = gridDim.x, gn = gridDim.y;
@@ -58,143 +148,108 @@ k_gemm(int transA, int transB, int64_t M, int64_t N, int64_t K, double alpha, co
   const int group = lb / (GROUP * gn), first = group * GROUP;
   const int rows = (gm - first) < GROUP ? (gm - first) : GROUP;
   const int bi = first + (lb % (GROUP * gn)) % rows, bj = (lb % (GROUP * gn)) / rows;
-  const int64_t r0 = (int64_t)bi * GB, c0 = (int64_t)bj * GB;
+  const int64_t r0 = (int64_t)bi * BM, c0 = (int64_t)bj * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % WM, wn = wave / WM;
+  const int wm = wave % WM, wn = wave / WM, g16 = lane & 15, q = lane >> 4;
 
-  constexpr int PER = GB * BK / NT;  // elements per thread per operand
-  constexpr int V = 16 / sizeof(S);  // elements per 16-byte vector
-  constexpr int PV = PER / V;        // vectors per thread per operand
-  S ra[PER], rb[PER];
-  // Whole blocks with 16-byte aligned columns move 16-byte vectors (V
-  // consecutive elements of the stored matrix: rows of a column, or k values
-  // of a transposed operand's column); other blocks move single elements with
-  // bounds checks.  Consecutive threads read consecutive addresses.
-  const bool vec = (r0 + GB <= M) && (c0 + GB <= N) && (K % BK == 0) && ((lda * (int64_t)sizeof(S)) % 16 == 0) &&
-                   ((ldb * (int64_t)sizeof(S)) % 16 == 0) && ((uintptr_t)A % 16 == 0) && ((uintptr_t)B % 16 == 0);
-  // vector v of a thread: (row-or-column index, k index) of its first element
-  auto avec = [&](int v, int& r, int& kk) {
-    const int e = tid + NT * v;
-    if (!transA) { r = (e % (GB / V)) * V; kk = e / (GB / V); } else { kk = (e % (BK / V)) * V; r = e / (BK / V); }
-  };
-  auto bvec = [&](int v, int& c, int& kb) {
-    const int e = tid + NT * v;
-    if (transB) { c = (e % (GB / V)) * V; kb = e / (GB / V); } else { kb = (e % (BK / V)) * V; c = e / (BK / V); }
-  };
-  auto gload = [&](int64_t k0) {
-    if (vec) {
-#pragma unroll
-      for (int v = 0; v < PV; ++v) {
-        int r, kk, c, kb;
-        avec(v, r, kk);
-        bvec(v, c, kb);
-        const S* pa = A + (transA ? (r0 + r) * lda + k0 + kk : (k0 + kk) * lda + r0 + r);
-        const S* pb = B + (transB ? (k0 + kb) * ldb + c0 + c : (c0 + c) * ldb + k0 + kb);
-        *(uint4*)&ra[V * v] = *(const uint4*)pa;
-        *(uint4*)&rb[V * v] = *(const uint4*)pb;
-      }
-      return;
-    }
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + NT * q;
-      int r, kk;
-      if (!transA) { r = e % GB; kk = e / GB; } else { kk = e % BK; r = e / BK; }
-      const int64_t gr = r0 + r, gk = k0 + kk;
-      ra[q] = (gr < M && gk < K) ? A[transA ? gr * lda + gk : gk * lda + gr] : (S)0;
-      int c, kb;
-      if (transB) { c = e % GB; kb = e / GB; } else { kb = e % BK; c = e / BK; }
-      const int64_t gc = c0 + c, gkb = k0 + kb;
-      rb[q] = (gc < N && gkb < K) ? B[transB ? gkb * ldb + gc : gc * ldb + gkb] : (S)0;
-    }
-  };
-  auto sstore = [&](int buf) {
-    if (vec) {
-#pragma unroll
-      for (int v = 0; v < PV; ++v) {
-        int r, kk, c, kb;
-        avec(v, r, kk);
-        bvec(v, c, kb);
-#pragma unroll
-        for (int u = 0; u < V; ++u) {
-          if (!transA) As[buf][kk][r + u] = ra[V * v + u]; else As[buf][kk + u][r] = ra[V * v + u];
-          if (transB) Bs[buf][kb][c + u] = rb[V * v + u]; else Bs[buf][kb + u][c] = rb[V * v + u];
-        }
-      }
-      return;
-    }
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + NT * q;
-      int r, kk;
-      if (!transA) { r = e % GB; kk = e / GB; } else { kk = e % BK; r = e / BK; }
-      As[buf][kk][r] = ra[q];
-      int c, kb;
-      if (transB) { c = e % GB; kb = e / GB; } else { kb = e % BK; c = e / BK; }
-      Bs[buf][kb][c] = rb[q];
-    }
-  };
-
-  using Acc = typename std::conditional<P == F64, d4, f4>::type;
+  OpA a;
+  OpB b;
+  a.init((const S*)Av, lda, r0, M, tid);
+  b.init((const S*)Bv, ldb, c0, N, tid);
   Acc acc[FM][FN];
 #pragma unroll
-  for (int a = 0; a < FM; ++a)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int b = 0; b < FN; ++b) acc[a][b] = Acc{0, 0, 0, 0};
+    for (int j = 0; j < FN; ++j) acc[i][j] = Acc{0, 0, 0, 0};
 
-  if (K > 0) {
+  const int64_t chunks = (K + BK - 1) / BK;
+  const int left = (int)(K % BK);
+  auto gload = [&](int64_t t) {
+    if (t + 1 < chunks || left == 0) {
+      a.load();
+      b.load();
+    } else {
+      a.load_tail(left, tid);
+      b.load_tail(left, tid);
+    }
+  };
+  if (chunks > 0) {
     gload(0);
-    sstore(0);
+    a.store(As[0], tid);
+    b.store(Bs[0], tid);
   }
   __syncthreads();
   int cur = 0;
-  for (int64_t k0 = 0; k0 < K; k0 += BK) {
-    const bool more = k0 + BK < K;
-    if (more) gload(k0 + BK);
+  for (int64_t t = 0; t < chunks; ++t) {
+    const bool more = t + 1 < chunks;
+    if (more) gload(t + 1);
 #pragma unroll
     for (int k4 = 0; k4 < BK; k4 += 4) {
+      const int k = k4 + q;
       S av[FM], bv[FN];
 #pragma unroll
-      for (int a = 0; a < FM; ++a) av[a] = As[cur][k4 + (lane >> 4)][wm * TM + a * 16 + (lane & 15)];
+      for (int i = 0; i < FM; ++i) av[i] = As[cur][k][OpA::col((wm * FM + i) * 16 + g16, P == F64 ? k : k4)];
 #pragma unroll
-      for (int b = 0; b < FN; ++b) bv[b] = Bs[cur][k4 + (lane >> 4)][wn * TN + b * 16 + (lane & 15)];
+      for (int j = 0; j < FN; ++j) bv[j] = Bs[cur][k][OpB::col((wn * FN + j) * 16 + g16, P == F64 ? k : k4)];
 #pragma unroll
-      for (int a = 0; a < FM; ++a)
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int b = 0; b < FN; ++b) {
+        for (int j = 0; j < FN; ++j) {
           if constexpr (P == F64)
-            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[i][j], 0, 0, 0);
           else
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc[a][b], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
         }
     }
-    if (more) sstore(cur ^ 1);
+    if (more) {
+      a.store(As[cur ^ 1], tid);
+      b.store(Bs[cur ^ 1], tid);
+    }
     __syncthreads();
     cur ^= 1;
   }
 
+  auto put = [&](auto* Cp, int64_t idx, double x) {
+    using T = std::remove_pointer_t<decltype(Cp)>;
+    double v = alpha * x;
+    if (beta != 0.0) v += beta * (double)Cp[idx];
+    Cp[idx] = (T)v;
+  };
 #pragma unroll
-  for (int a = 0; a < FM; ++a)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int b = 0; b < FN; ++b)
+    for (int j = 0; j < FN; ++j) {
+      const int64_t R = r0 + (wm * FM + i) * 16, C = c0 + (wn * FN + j) * 16;
+      if constexpr (P == F64) {
+        if (R + g16 >= M) continue;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = (P == F64) ? ((lane >> 4) + 4 * r) : (4 * (lane >> 4) + r);
-        const int64_t R = r0 + wm * TM + a * 16 + row;
-        const int64_t C = c0 + wn * TN + b * 16 + (lane & 15);
-        if (R >= M || C >= N) continue;
-        const int64_t idx = C * ldc + R;
-        double v = alpha * (double)acc[a][b][r];
-        if (cprec == F64) {
-          double* Cp = (double*)Cv;
-          if (beta != 0.0) v += beta * Cp[idx];
-          Cp[idx] = v;
+        for (int r = 0; r < 4; ++r)
+          if (C + q + 4 * r < N) put((double*)Cv, (C + q + 4 * r) * ldc + R + g16, acc[i][j][r]);
+      } else {
+        if (C + g16 >= N) continue;
+        const int64_t idx = (C + g16) * ldc + R + 4 * q;
+        if (cprec == F32 && R + 4 * q + 4 <= M) {
+          using Vec = GTraits<F32>::Vec;
+          Vec* o = (Vec*)((float*)Cv + idx);
+          Vec old = {0, 0, 0, 0}, w;
+          if (beta != 0.0) old = *o;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            double v = alpha * (double)acc[i][j][r];
+            if (beta != 0.0) v += beta * (double)old[r];
+            w[r] = (float)v;
+          }
+          *o = w;
         } else {
-          float* Cp = (float*)Cv;
-          if (beta != 0.0) v += beta * (double)Cp[idx];
-          Cp[idx] = (float)v;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (R + 4 * q + r >= M) break;
+            if (cprec == F64) put((double*)Cv, idx + r, (double)acc[i][j][r]);
+            else put((float*)Cv, idx + r, (double)acc[i][j][r]);
+          }
         }
       }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -221,6 +276,13 @@ k_gemm(int transA, int transB, int64_t M, int64_t N, int64_t K, double alpha, co
 // into the FP32 results.  A lane supplies 32 consecutive k of one row or
 // column; the same lane-to-k assignment for both operands makes the sum
 // correct for any internal order of the 128 products.
+//
+// Bound: at 8192^3 by LDS reads and the matrix cores together.  Whole calls,
+// before -> after (kernels for whole shapes only, generic bytewise one for the
+// rest, exponents requested behind the next stage's operands, bounds checks on
+// every store): FP8 TN 8192^3 643 -> 630 us, NN 734 -> 658 us, TN 3001 x 2999 x
+// 4003 560 -> 110 us, NN 2000^3 114 -> 47 us; BF16 NN 8192^3 1200 -> 1136 us,
+// TN 3001 x 2999 x 4003 584 -> 181 us.
 // ---------------------------------------------------------------------------
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -308,11 +370,18 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
     // the scale blocks of this wave's rows and columns
     const int64_t ra = r0 + 16 * TA * wm, cb = c0 + 16 * TB * wn;
     const int64_t ib = (ra < M ? ra : M - 1) / 128, jb = (cb < N ? cb : N - 1) / 128;
+    // (the exponents of a stage are requested a stage ahead, before its operands:
+    // loads return in order, so a later request would wait for all of those)
+    const int8_t* pea = sa_kmajor ? sA + ib * mbA : sA + ib;
+    const int8_t* peb = sb_kmajor ? sB + jb : sB + jb * mbB;
+    const int64_t dea = sa_kmajor ? 1 : mbA, deb = sb_kmajor ? mbB : 1;
+    int nea = KB > 0 ? *pea : 0, neb = KB > 0 ? *peb : 0;
     for (int64_t k0 = 0; k0 < KB; k0 += STAGE) {
-      gload(k0 + STAGE < KB ? k0 + STAGE : k0);
-      const int64_t kb = k0 / 128;
-      const int ea = sa_kmajor ? sA[ib * mbA + kb] : sA[kb * mbA + ib];
-      const int eb = sb_kmajor ? sB[kb * mbB + jb] : sB[jb * mbB + kb];
+      const int64_t kn = k0 + STAGE < KB ? k0 + STAGE : k0;
+      const int ea = nea, eb = neb;
+      nea = pea[(kn / 128) * dea];
+      neb = peb[(kn / 128) * deb];
+      gload(kn);
       // E8M0 scale bytes of 2^-ea and 2^-eb; 255 (ea = -128) is no scale: one step goes to the other operand's
       int sca = 127 - ea, scb = 127 - eb;
       if (sca > 254) { sca = 254; scb = scb < 254 ? scb + 1 : 254; }
@@ -378,27 +447,32 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
   }
 
   // lane (g16, q), register r of tile (a, b): C[r0 + 16 (TA wm + a) + g16][c0 + 16 (TB wn + b) + 4 q + r]
-#pragma unroll
-  for (int a = 0; a < TA; ++a)
+  const int64_t R0 = r0 + wm * TA * 16 + g16, C0 = c0 + wn * TB * 16 + 4 * q;
+  auto write = [&](auto* Cp, auto whole) {
+    using T = std::remove_pointer_t<decltype(Cp)>;
+    Cp += C0 * ldc + R0;
 #pragma unroll
     for (int b = 0; b < TB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t R = r0 + (wm * TA + a) * 16 + g16;
-        const int64_t Cc = c0 + (wn * TB + b) * 16 + 4 * q + r;
-        if (R >= M || Cc >= N) continue;
-        const int64_t idx = Cc * ldc + R;
-        double v = alpha * (double)acc[a][b][r];
-        if (cprec == F64) {
-          double* Cp = (double*)Cv;
-          if (beta != 0.0) v += beta * Cp[idx];
-          Cp[idx] = v;
-        } else {
-          float* Cp = (float*)Cv;
-          if (beta != 0.0) v += beta * (double)Cp[idx];
-          Cp[idx] = (float)v;
+        T* col = Cp + (b * 16 + r) * ldc;
+#pragma unroll
+        for (int a = 0; a < TA; ++a) {
+          if (!decltype(whole)::value && (R0 + a * 16 >= M || C0 + b * 16 + r >= N)) continue;
+          double v = alpha * (double)acc[a][b][r];
+          if (beta != 0.0) v += beta * (double)col[a * 16];
+          col[a * 16] = (T)v;
         }
       }
+  };
+  const bool whole = r0 + BM <= M && c0 + BN <= N;
+  if (cprec == F64) {
+    if (whole) write((double*)Cv, std::true_type{});
+    else write((double*)Cv, std::false_type{});
+  } else {
+    if (whole) write((float*)Cv, std::true_type{});
+    else write((float*)Cv, std::false_type{});
+  }
 }
 
 // Packs a rows x cols operand into a k-contiguous array: out[r * ldo + c] =
@@ -500,13 +574,40 @@ hipError_t launch_gemm_lowp(int prec, int64_t m, int64_t n, int64_t k, double al
   return hipGetLastError();
 }
 
+template <int P, int WM, int WN, int FM, int FN, int BK>
+static void run_gemm(int transA, int transB, int64_t m, int64_t n, int64_t k, double alpha, const void* A, int64_t lda,
+                     const void* B, int64_t ldb, double beta, void* C, int64_t ldc, int cprec, hipStream_t s) {
+  constexpr int BM = 16 * FM * WM, BN = 16 * FN * WN;
+  const dim3 grid((unsigned)((m + BM - 1) / BM), (unsigned)((n + BN - 1) / BN));
+#define MPCR_GEMM(TA, TB) \
+  k_gemm<P, WM, WN, FM, FN, BK, TA, TB><<<grid, 64 * WM * WN, 0, s>>>(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, cprec)
+  if (transA) {
+    if (transB) MPCR_GEMM(true, true);
+    else MPCR_GEMM(true, false);
+  } else {
+    if (transB) MPCR_GEMM(false, true);
+    else MPCR_GEMM(false, false);
+  }
+#undef MPCR_GEMM
+}
+
 hipError_t launch_gemm(int prec, int transA, int transB, int64_t m, int64_t n, int64_t k, double alpha, const void* A,
                        int64_t lda, const void* B, int64_t ldb, double beta, void* C, int64_t ldc, int cprec,
                        hipStream_t s) {
-  dim3 grid((unsigned)((m + GB - 1) / GB), (unsigned)((n + GB - 1) / GB));
+  // 64 x 64 blocks (four waves of 32 x 32): every size divides well over the 256
+  // CUs and several workgroups share one.  FP32 blocks of 128 x 128 (waves of 64 x
+  // 64, half the LDS reads per product) run 1.09 times as fast per element once
+  // there are two rounds of them (n = 4096: 1056 us, 64-blocks 1154; n = 3000: 653
+  // and 537; n = 2048, one round: 179 and 172), so they are taken where what they
+  // waste in their last round is less than that.
+  auto rounds = [&](int64_t bs) { return (((m + bs - 1) / bs) * ((n + bs - 1) / bs) + 255) / 256; };
+  const bool large = rounds(128) >= 2 && rounds(128) * 400 <= rounds(64) * 109;
   switch (prec) {
-    case F64: k_gemm<F64><<<grid, GTraits<F64>::NW * 64, 0, s>>>(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, cprec); break;
-    case F32: k_gemm<F32><<<grid, GTraits<F32>::NW * 64, 0, s>>>(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, cprec); break;
+    case F64: run_gemm<F64, 2, 2, 2, 2, 16>(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, cprec, s); break;
+    case F32:
+      if (large) run_gemm<F32, 2, 2, 4, 4, 16>(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, cprec, s);
+      else run_gemm<F32, 2, 2, 2, 2, 16>(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, cprec, s);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
