@@ -287,17 +287,15 @@ hipError_t launch_tile_update_16(const TileView& tv, int k, int cfmt, const Gemm
 hipError_t launch_logdet(const TileView& tv, double* out, hipStream_t s);
 hipError_t launch_trtri_diag(const TileView& tv, double* Linv, const double* dinv, hipStream_t s);
 
-// One step of the tile sweeps: the diag launch solves block k (and writes it
-// by rows into stage, nb x nrhs), the update launch subtracts its product from
-// the remaining blocks, reading the right-hand side from stage.
-hipError_t launch_fwd_diag(const TileView& tv, const double* Linv, int k, double* R, double* W,
-                           int64_t ld, int nrhs, double* stage, hipStream_t s);
-hipError_t launch_fwd_update(const TileView& tv, int k, double* R, const double* stage, int64_t ld, int nrhs,
-                             hipStream_t s);
-hipError_t launch_bwd_diag(const TileView& tv, const double* Linv, int k, double* R, double* X,
-                           int64_t ld, int nrhs, double* stage, hipStream_t s);
-hipError_t launch_bwd_update(const TileView& tv, int k, double* R, const double* stage, int64_t ld, int nrhs,
-                             hipStream_t s);
+// pair (nt / 2 tiles of nb x nb): the off-diagonal tiles of the inverses of the
+// pairs of diagonal tiles, from the inverted tiles Linv and the factor
+hipError_t launch_pair_inverse(const TileView& tv, const double* Linv, double* pair, hipStream_t s);
+// out = L^{-1} in (forward) or L^{-T} in over the tiles, by steps of two tiles with
+// pair and of one without (NULL); V receives the updated
+// right-hand sides, stage (2 nb x nrhs) the solved ones of a step by rows.  in,
+// V and out are different blocks.
+hipError_t launch_sweep(const TileView& tv, bool forward, const double* Linv, const double* pair, const double* in,
+                        double* V, double* out, int64_t ld, int nrhs, double* stage, hipStream_t s);
 
 // R = B - Sigma X (B == NULL: R = -Sigma X); rowsum != NULL also receives sum_c |Sigma_rc|
 hipError_t launch_residual_cov(int n, const double* locs, const mpcr_theta_t& th, const double* B,

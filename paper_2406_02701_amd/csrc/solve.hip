@@ -3,11 +3,18 @@
 // Forward solve L W = B and backward solve L^T X = W over the tile factor (the
 // paper's forwardsolve / backsolve pair of the MLE section), with the inverted
 // FP64 diagonal tiles (each stored by rows, i.e. Linv_kk^T in column-major order):
-//   forward,  k = 0 .. nt-1:  W_k = Linv_kk R_k ;  R_i -= L_ik W_k   (i > k)
-//   backward, k = nt-1 .. 0:  X_k = Linv_kk^T V_k ; V_i -= L_ki^T X_k (i < k)
+//   forward,  k = 0 .. :  W_k = Linv_k R_k ;  R_i -= L_ik W_k   (i > k)
+//   backward, .. k = 0:   X_k = Linv_k^T V_k ; V_i -= L_ki^T X_k (i < k)
+// The steps k go by tiles, or by pairs of tiles: then a step's Linv_k is the inverse
+// of the 2 x 2 tile block [[A, 0], [B, C]] on the diagonal, [[A', 0], [-C' B A',
+// C']], whose third tile k_pair_inverse forms.  A step costs two launches on the
+// critical path whatever its width, so pairs pay from the second solve with a
+// factor on.
 // Off-diagonal tiles are read in their storage format and widened to FP64.
 // All right-hand-side blocks are column-major with leading dimension ld >= the
 // padded order nt*nb; padded rows are kept at zero.
+#include <type_traits>
+
 #include "mpcr_internal.h"
 
 namespace mpcr {
@@ -132,51 +139,59 @@ __device__ __forceinline__ void mfma_span(const void* M, int64_t ldm, int64_t ro
   }
 }
 
-// out[r0 .. r0+15][c] (op)= sum_k op(M)[r0 + .., k] V[k][c] over one nb x nb tile M
-// (format F, column-major); V[k][c] at V[k * vsk + c * vsc]; mode 0:
-// out = product, mode 1: out -= product.  With copy (mode 0), the result is
-// also written by rows: copy[row * nrhs + c].
-template <int F, bool TRANS>
-__device__ void tile_mfma(const void* M, int nb, int r0, const double* V, int64_t vsc, int64_t vsk, double* out,
-                          int64_t ldo, int nrhs, int mode, double (*red)[16][17], double mul = 1.0,
-                          double* copy = nullptr) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int q = lane >> 4, c = lane & 15;
-  const int kw = nb / SW;
-  // one 16-column chunk of right-hand sides per workgroup row of the grid
-  for (int c0 = blockIdx.y * RHS_CHUNK; c0 < nrhs && c0 < (int)(blockIdx.y + 1) * RHS_CHUNK; c0 += RHS_CHUNK) {
-    const int nc = (nrhs - c0) < RHS_CHUNK ? (nrhs - c0) : RHS_CHUNK;
-    d4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
-    mfma_span<F, TRANS>(M, nb, r0 + c, w * kw, (w + 1) * kw, c < nc ? V + (int64_t)(c0 + c) * vsc : nullptr, vsk,
-                        lane, acc0, acc1, mul);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) red[w][q + 4 * r][c] = acc0[r] + acc1[r];
-    __syncthreads();
-    if (w == 0 && c < nc) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int rr = q + 4 * r;
-        double v = red[0][rr][c];
-#pragma unroll
-        for (int x = 1; x < SW; ++x) v += red[x][rr][c];
-        double* o = out + (int64_t)(c0 + c) * ldo + r0 + rr;
-        *o = mode == 0 ? v : *o - v;
-        if (copy) copy[(int64_t)(r0 + rr) * nrhs + c0 + c] = v;
-      }
-    }
-    __syncthreads();
+// One nb x nb tile of a product (format f, FP8 multiplier mul) and the block of
+// right-hand sides it multiplies, element (k, c) at V[k * vsk + c * vsc].
+struct Term {
+  const void* M;
+  int f;
+  double mul;
+  const double* V;
+  int64_t vsc, vsk;
+};
+
+template <bool TRANS>
+__device__ __forceinline__ void span_any(const Term& t, int64_t ldm, int64_t row, int k0, int k1, const double* V, int lane,
+                                         d4& acc0, d4& acc1) {
+  switch (t.f) {
+    case F64: mfma_span<F64, TRANS>(t.M, ldm, row, k0, k1, V, t.vsk, lane, acc0, acc1); break;
+    case F32: mfma_span<F32, TRANS>(t.M, ldm, row, k0, k1, V, t.vsk, lane, acc0, acc1); break;
+    case F16: mfma_span<F16, TRANS>(t.M, ldm, row, k0, k1, V, t.vsk, lane, acc0, acc1); break;
+    case BF16: mfma_span<BF16, TRANS>(t.M, ldm, row, k0, k1, V, t.vsk, lane, acc0, acc1); break;
+    default: mfma_span<F8, TRANS>(t.M, ldm, row, k0, k1, V, t.vsk, lane, acc0, acc1, t.mul); break;
   }
 }
 
-template <bool TRANS>
-__device__ void tile_mfma_any(const void* M, int f, double mul, int nb, int r0, const double* V, int64_t vsc,
-                              int64_t vsk, double* out, int64_t ldo, int nrhs, int mode, double (*red)[16][17]) {
-  switch (f) {
-    case F64: tile_mfma<F64, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, mode, red); break;
-    case F32: tile_mfma<F32, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, mode, red); break;
-    case F16: tile_mfma<F16, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, mode, red); break;
-    case BF16: tile_mfma<BF16, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, mode, red); break;
-    default: tile_mfma<F8, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, mode, red, mul); break;
+// out[r0 .. r0+15][c] = sum over the n (1 or 2) tiles of op(M)[r0 + .., :] V[:][c]
+// (in == NULL) or in[..][c] minus it (in may be out).  The waves divide the whole
+// contraction, so that each has to do with one tile.  With copy, the result is
+// also written by rows: copy[row * nrhs + c].  ONLY64: all tiles are FP64.
+template <bool TRANS, bool ONLY64, class GetTerm>
+__device__ __forceinline__ void tile_mfma(int n, GetTerm term, int nb, int r0, const double* in, double* out, int64_t ldo,
+                                          int nrhs, double (*red)[16][17], double* copy = nullptr) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = lane >> 4, c = lane & 15;
+  const int kw = nb * n / SW, x = w * n / SW, k0 = w * kw - x * nb;
+  // one 16-column chunk of right-hand sides per workgroup row of the grid
+  const int c0 = blockIdx.y * RHS_CHUNK, nc = min(RHS_CHUNK, nrhs - c0);
+  d4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+  const Term t = term(x);
+  const double* V = c < nc ? t.V + (int64_t)(c0 + c) * t.vsc : nullptr;
+  if constexpr (ONLY64) mfma_span<F64, TRANS>(t.M, nb, r0 + c, k0, k0 + kw, V, t.vsk, lane, acc0, acc1);
+  else span_any<TRANS>(t, nb, r0 + c, k0, k0 + kw, V, lane, acc0, acc1);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[w][q + 4 * r][c] = acc0[r] + acc1[r];
+  __syncthreads();
+  if (w == 0 && c < nc) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int rr = q + 4 * r;
+      double v = red[0][rr][c];
+#pragma unroll
+      for (int y = 1; y < SW; ++y) v += red[y][rr][c];
+      const int64_t e = (int64_t)(c0 + c) * ldo + r0 + rr;
+      out[e] = in ? in[e] - v : v;
+      if (copy) copy[(int64_t)(r0 + rr) * nrhs + c0 + c] = v;
+    }
   }
 }
 
@@ -239,148 +254,258 @@ __device__ __forceinline__ void mfma_span4(const void* M, int64_t ldm, int64_t r
   }
 }
 
-// out[r0 .. r0+63][c] -= sum_k op(M)[r0 + .., k] V[k][c]; V[k][c] at V[k * vsk + c * vsc];
+// out[r0 .. r0+63][c] = in[..][c] - sum over the n tiles of op(M)[r0 + .., :] V[:][c];
 // the waves' partial products are added in a fixed order
-template <int F, bool TRANS>
-__device__ void tile_mfma4(const void* M, int nb, int r0, const double* V, int64_t vsc, int64_t vsk, double* out,
-                           int64_t ldo, int nrhs, double (*red)[64][17], double mul) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+template <bool TRANS, class GetTerm>
+__device__ __forceinline__ void tile_mfma4(int n, GetTerm term, int nb, int r0, const double* in, double* out, int64_t ldo,
+                                           int nrhs, double (*red)[64][17]) {
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, c = lane & 15;
-  const int kw = nb / SW4;
-  for (int c0 = blockIdx.y * RHS_CHUNK; c0 < nrhs && c0 < (int)(blockIdx.y + 1) * RHS_CHUNK; c0 += RHS_CHUNK) {
-    const int nc = (nrhs - c0) < RHS_CHUNK ? (nrhs - c0) : RHS_CHUNK;
-    d4 acc[4];
+  const int kw = nb * n / SW4, x = w * n / SW4, k0 = w * kw - x * nb, k1 = k0 + kw;
+  const int c0 = blockIdx.y * RHS_CHUNK, nc = min(RHS_CHUNK, nrhs - c0);
+  d4 acc[4];
 #pragma unroll
-    for (int h = 0; h < 4; ++h) acc[h] = d4{0, 0, 0, 0};
-    mfma_span4<F, TRANS>(M, nb, r0 + c, w * kw, (w + 1) * kw, c < nc ? V + (int64_t)(c0 + c) * vsc : nullptr, vsk,
-                         lane, acc, mul);
+  for (int h = 0; h < 4; ++h) acc[h] = d4{0, 0, 0, 0};
+  const Term t = term(x);
+  const double* V = c < nc ? t.V + (int64_t)(c0 + c) * t.vsc : nullptr;
+  switch (t.f) {
+    case F64: mfma_span4<F64, TRANS>(t.M, nb, r0 + c, k0, k1, V, t.vsk, lane, acc, 1.0); break;
+    case F32: mfma_span4<F32, TRANS>(t.M, nb, r0 + c, k0, k1, V, t.vsk, lane, acc, 1.0); break;
+    case F16: mfma_span4<F16, TRANS>(t.M, nb, r0 + c, k0, k1, V, t.vsk, lane, acc, 1.0); break;
+    case BF16: mfma_span4<BF16, TRANS>(t.M, nb, r0 + c, k0, k1, V, t.vsk, lane, acc, 1.0); break;
+    default: mfma_span4<F8, TRANS>(t.M, nb, r0 + c, k0, k1, V, t.vsk, lane, acc, t.mul); break;
+  }
 #pragma unroll
-    for (int h = 0; h < 4; ++h)
+  for (int h = 0; h < 4; ++h)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[w][16 * h + q + 4 * r][c] = acc[h][r];
-    __syncthreads();
-    for (int e = tid; e < 64 * RHS_CHUNK; e += 64 * SW4) {
-      const int rr = e % 64, cc = e / 64;
-      if (cc < nc) {
-        double v = red[0][rr][cc];
+    for (int r = 0; r < 4; ++r) red[w][16 * h + q + 4 * r][c] = acc[h][r];
+  __syncthreads();
+  for (int e = tid; e < 64 * RHS_CHUNK; e += 64 * SW4) {
+    const int rr = e % 64, cc = e / 64;
+    if (cc < nc) {
+      double v = red[0][rr][cc];
 #pragma unroll
-        for (int x = 1; x < SW4; ++x) v += red[x][rr][cc];
-        out[(int64_t)(c0 + cc) * ldo + r0 + rr] -= v;
-      }
+      for (int y = 1; y < SW4; ++y) v += red[y][rr][cc];
+      const int64_t o = (int64_t)(c0 + cc) * ldo + r0 + rr;
+      out[o] = in[o] - v;
     }
-    __syncthreads();
   }
 }
 
-template <bool TRANS>
-__device__ void tile_mfma4_any(const void* M, int f, double mul, int nb, int r0, const double* V, int64_t vsc,
-                               int64_t vsk, double* out, int64_t ldo, int nrhs, double (*red)[64][17]) {
-  switch (f) {
-    case F64: tile_mfma4<F64, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, red, mul); break;
-    case F32: tile_mfma4<F32, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, red, mul); break;
-    case F16: tile_mfma4<F16, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, red, mul); break;
-    case BF16: tile_mfma4<BF16, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, red, mul); break;
-    default: tile_mfma4<F8, TRANS>(M, nb, r0, V, vsc, vsk, out, ldo, nrhs, red, mul); break;
-  }
-}
+// Each step solves one or two tiles (diag kernel) and then updates the rest
+// (update kernel).  The update kernels hold every tile format's loop; they are
+// held to 128 VGPRs so that two 512-thread workgroups fit on a CU (with 156 VGPRs
+// only one did, which halved their bandwidth).  The diag kernel also writes the
+// solved block by rows into stage (2 nb x nrhs, row stride nrhs), which the update
+// kernel reads as its right-hand side: lanes then read whole rows of 16 values.
+// A launch takes about 5 us and its tiles' products little of that, so pairs halve
+// a sweep, and the first step reads the right-hand sides where they are (in) and
+// leaves the rest of them updated in the working copy.  Measured: an update with
+// one tile 5.0 us, with a pair 6.2 (n = 1024); a MALA iteration (four sweeps) at n
+// = 1024 310 -> 225 us.
 
-// Each step solves one block (diag kernel) and then updates the rest (update
-// kernel).  The update kernels hold every tile format's loop; they are held to
-// 128 VGPRs so that two 512-thread workgroups fit on a CU (with 156 VGPRs only
-// one did, which halved their bandwidth).  The diag kernel also writes the solved block by rows into stage
-// (nb x nrhs, row stride nrhs), which the update kernel reads as its
-// right-hand side: lanes then read whole rows of 16 values.
-
-// one workgroup per 16 output rows
-__global__ __launch_bounds__(STHREADS) void k_fwd_diag(int nb, const double* Linv, int k, const double* R, double* W,
-                                                       int64_t ld, int nrhs, const int* info, double* stage) {
+// one workgroup per 16 output rows; first: the step's first tile, cnt: its tiles
+__global__ __launch_bounds__(STHREADS) void k_fwd_diag(int nb, const double* Linv, const double* pair, int first,
+                                                       const double* R, double* W, int64_t ld, int nrhs, const int* info,
+                                                       double* stage) {
   if (*info) return;
   __shared__ double red[SW][16][17];
-  const int64_t off = (int64_t)k * nb;
-  tile_mfma<F64, true>(Linv + (int64_t)k * nb * nb, nb, blockIdx.x * 16, R + off, ld, 1, W + off, ld, nrhs, 0, red, 1.0,
-                       stage);
+  const int rb = nb / 16, h = blockIdx.x / rb;  // tile first + h: [A'] or [N, C']
+  const int64_t off = (int64_t)first * nb, nb2 = (int64_t)nb * nb;
+  auto term = [&](int x) {
+    const double* M = x < h ? pair + (int64_t)(first / 2) * nb2 : Linv + (first + h) * nb2;
+    return Term{M, F64, 1.0, R + off + (int64_t)x * nb, ld, 1};
+  };
+  tile_mfma<true, true>(h + 1, term, nb, (blockIdx.x % rb) * 16, nullptr, W + off + (int64_t)h * nb, ld, nrhs, red,
+                        stage + (int64_t)h * nb * nrhs);
 }
 
-__global__ __launch_bounds__(STHREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_update(TileView tv, int k, double* R, const double* stage,
-                                                         int64_t ld, int nrhs) {
+// X_k = Linv_k^T V_k: the stored (row-major) inverse read as column-major
+__global__ __launch_bounds__(STHREADS) void k_bwd_diag(int nb, const double* Linv, const double* pair, int first, int cnt,
+                                                       const double* V, double* X, int64_t ld, int nrhs, const int* info,
+                                                       double* stage) {
+  if (*info) return;
+  __shared__ double red[SW][16][17];
+  const int rb = nb / 16, h = blockIdx.x / rb;  // tile first + h: [A'^T, N^T] or [C'^T]
+  const int64_t off = (int64_t)first * nb, nb2 = (int64_t)nb * nb;
+  auto term = [&](int x) {
+    const double* M = x > 0 ? pair + (int64_t)(first / 2) * nb2 : Linv + (first + h) * nb2;
+    return Term{M, F64, 1.0, V + off + (int64_t)(h + x) * nb, ld, 1};
+  };
+  tile_mfma<false, true>(cnt - h, term, nb, (blockIdx.x % rb) * 16, nullptr, X + off + (int64_t)h * nb, ld, nrhs, red,
+                         stage + (int64_t)h * nb * nrhs);
+}
+
+// R_i = in_i - L_ik W_k for the tiles i behind the step's
+__device__ __forceinline__ Term fwd_term(const TileView& tv, int i, int first, int x, const double* stage, int nrhs) {
+  return {tv.tile(i, first + x), tv.tfmt(i, first + x), tv.tmul(i, first + x), stage + (int64_t)x * tv.nb * nrhs, 1, nrhs};
+}
+__device__ __forceinline__ Term bwd_term(const TileView& tv, int i, int first, int x, const double* stage, int nrhs) {
+  return {tv.tile(first + x, i), tv.tfmt(first + x, i), tv.tmul(first + x, i), stage + (int64_t)x * tv.nb * nrhs, 1, nrhs};
+}
+
+__global__ __launch_bounds__(STHREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_update(
+    TileView tv, int first, int cnt, const double* in, double* R, const double* stage, int64_t ld, int nrhs) {
   if (*tv.info) return;
   __shared__ double red[SW][16][17];
   const int nb = tv.nb, rb = nb / 16;
-  const int i = k + 1 + blockIdx.x / rb;
-  tile_mfma_any<false>(tv.tile(i, k), tv.tfmt(i, k), tv.tmul(i, k), nb, (blockIdx.x % rb) * 16, stage, 1, nrhs,
-                       R + (int64_t)i * nb, ld, nrhs, 1, red);
+  const int i = first + cnt + blockIdx.x / rb;
+  tile_mfma<false, false>(cnt, [&](int x) { return fwd_term(tv, i, first, x, stage, nrhs); }, nb, (blockIdx.x % rb) * 16,
+                          in + (int64_t)i * nb, R + (int64_t)i * nb, ld, nrhs, red);
 }
 
-// X_k = Linv_kk^T V_k: the stored (row-major) inverse read as column-major
-__global__ __launch_bounds__(STHREADS) void k_bwd_diag(int nb, const double* Linv, int k, const double* V, double* X,
-                                                       int64_t ld, int nrhs, const int* info, double* stage) {
-  if (*info) return;
-  __shared__ double red[SW][16][17];
-  const int64_t off = (int64_t)k * nb;
-  tile_mfma<F64, false>(Linv + (int64_t)k * nb * nb, nb, blockIdx.x * 16, V + off, ld, 1, X + off, ld, nrhs, 0, red,
-                        1.0, stage);
-}
-
-__global__ __launch_bounds__(STHREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_update(TileView tv, int k, double* V, const double* stage,
-                                                         int64_t ld, int nrhs) {
+__global__ __launch_bounds__(STHREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_update(
+    TileView tv, int first, int cnt, const double* in, double* V, const double* stage, int64_t ld, int nrhs) {
   if (*tv.info) return;
   __shared__ double red[SW][16][17];
   const int nb = tv.nb, rb = nb / 16;
-  const int i = blockIdx.x / rb;  // i < k
-  tile_mfma_any<true>(tv.tile(k, i), tv.tfmt(k, i), tv.tmul(k, i), nb, (blockIdx.x % rb) * 16, stage, 1, nrhs,
-                      V + (int64_t)i * nb, ld, nrhs, 1, red);
+  const int i = blockIdx.x / rb;  // i < first
+  tile_mfma<true, false>(cnt, [&](int x) { return bwd_term(tv, i, first, x, stage, nrhs); }, nb, (blockIdx.x % rb) * 16,
+                         in + (int64_t)i * nb, V + (int64_t)i * nb, ld, nrhs, red);
 }
 
-__global__ __launch_bounds__(64 * SW4) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_update4(TileView tv, int k, double* R, const double* stage, int64_t ld,
-                                                     int nrhs) {
+__global__ __launch_bounds__(64 * SW4) __attribute__((amdgpu_waves_per_eu(4))) void k_fwd_update4(
+    TileView tv, int first, int cnt, const double* in, double* R, const double* stage, int64_t ld, int nrhs) {
   if (*tv.info) return;
   __shared__ double red[SW4][64][17];
   const int nb = tv.nb, rb = nb / 64;
-  const int i = k + 1 + blockIdx.x / rb;
-  tile_mfma4_any<false>(tv.tile(i, k), tv.tfmt(i, k), tv.tmul(i, k), nb, (blockIdx.x % rb) * 64, stage, 1, nrhs,
-                        R + (int64_t)i * nb, ld, nrhs, red);
+  const int i = first + cnt + blockIdx.x / rb;
+  tile_mfma4<false>(cnt, [&](int x) { return fwd_term(tv, i, first, x, stage, nrhs); }, nb, (blockIdx.x % rb) * 64,
+                    in + (int64_t)i * nb, R + (int64_t)i * nb, ld, nrhs, red);
 }
 
-__global__ __launch_bounds__(64 * SW4) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_update4(TileView tv, int k, double* V, const double* stage, int64_t ld,
-                                                     int nrhs) {
+__global__ __launch_bounds__(64 * SW4) __attribute__((amdgpu_waves_per_eu(4))) void k_bwd_update4(
+    TileView tv, int first, int cnt, const double* in, double* V, const double* stage, int64_t ld, int nrhs) {
   if (*tv.info) return;
   __shared__ double red[SW4][64][17];
   const int nb = tv.nb, rb = nb / 64;
-  const int i = blockIdx.x / rb;  // i < k
-  tile_mfma4_any<true>(tv.tile(k, i), tv.tfmt(k, i), tv.tmul(k, i), nb, (blockIdx.x % rb) * 64, stage, 1, nrhs,
-                       V + (int64_t)i * nb, ld, nrhs, red);
+  const int i = blockIdx.x / rb;  // i < first
+  tile_mfma4<true>(cnt, [&](int x) { return bwd_term(tv, i, first, x, stage, nrhs); }, nb, (blockIdx.x % rb) * 64,
+                   in + (int64_t)i * nb, V + (int64_t)i * nb, ld, nrhs, red);
 }
 
 constexpr int WIDE_MIN_TILES = 16;  // update launches over at least this many tiles use 64-row workgroups
-static unsigned nchunk(int nrhs) { return (unsigned)((nrhs + RHS_CHUNK - 1) / RHS_CHUNK); }
 
-hipError_t launch_fwd_diag(const TileView& tv, const double* Linv, int k, double* R, double* W, int64_t ld,
-                           int nrhs, double* stage, hipStream_t s) {
-  k_fwd_diag<<<dim3(tv.nb / 16, nchunk(nrhs)), STHREADS, 0, s>>>(tv.nb, Linv, k, R, W, ld, nrhs, tv.info, stage);
+hipError_t launch_sweep(const TileView& tv, bool forward, const double* Linv, const double* pair, const double* in,
+                        double* V, double* out, int64_t ld, int nrhs, double* stage, hipStream_t s) {
+  const int nb = tv.nb, rb = nb / 16, width = pair ? 2 : 1, steps = (tv.nt + width - 1) / width;
+  const unsigned chunks = (unsigned)((nrhs + RHS_CHUNK - 1) / RHS_CHUNK);
+  const double* cur = in;
+  for (int p = 0; p < steps; ++p) {
+    const int first = width * (forward ? p : steps - 1 - p), cnt = tv.nt - first < width ? tv.nt - first : width;
+    const int rest = forward ? tv.nt - first - cnt : first;  // tiles still to be updated
+    const dim3 diag(cnt * rb, chunks), wide(rest * (nb / 64), chunks), narrow(rest * rb, chunks);
+    if (forward) {
+      k_fwd_diag<<<diag, STHREADS, 0, s>>>(nb, Linv, pair, first, cur, out, ld, nrhs, tv.info, stage);
+      if (rest >= WIDE_MIN_TILES) k_fwd_update4<<<wide, 64 * SW4, 0, s>>>(tv, first, cnt, cur, V, stage, ld, nrhs);
+      else if (rest > 0) k_fwd_update<<<narrow, STHREADS, 0, s>>>(tv, first, cnt, cur, V, stage, ld, nrhs);
+    } else {
+      k_bwd_diag<<<diag, STHREADS, 0, s>>>(nb, Linv, pair, first, cnt, cur, out, ld, nrhs, tv.info, stage);
+      if (rest >= WIDE_MIN_TILES) k_bwd_update4<<<wide, 64 * SW4, 0, s>>>(tv, first, cnt, cur, V, stage, ld, nrhs);
+      else if (rest > 0) k_bwd_update<<<narrow, STHREADS, 0, s>>>(tv, first, cnt, cur, V, stage, ld, nrhs);
+    }
+    cur = V;
+  }
   return hipGetLastError();
 }
-hipError_t launch_fwd_update(const TileView& tv, int k, double* R, const double* stage, int64_t ld, int nrhs,
-                             hipStream_t s) {
-  int nt = tv.nt - k - 1;
-  if (nt <= 0) return hipSuccess;
-  if (nt >= WIDE_MIN_TILES)
-    k_fwd_update4<<<dim3(nt * (tv.nb / 64), nchunk(nrhs)), 64 * SW4, 0, s>>>(tv, k, R, stage, ld, nrhs);
-  else
-    k_fwd_update<<<dim3(nt * (tv.nb / 16), nchunk(nrhs)), STHREADS, 0, s>>>(tv, k, R, stage, ld, nrhs);
-  return hipGetLastError();
+
+// The third tile N = -C' B A' of the inverse of every pair of diagonal tiles
+// [[A, 0], [B, C]], stored by rows like A' and C'.  One workgroup per 16 columns of
+// N: U = B A' into LDS (nb x 16), whose operands are both read 16 consecutive
+// elements at a time, then -C' U; waves take 16-row tiles in turn.  C' and A' are
+// lower triangular: their zeros are left out by 64-wide blocks.  FP64 MFMA, operands
+// straight from memory, 64 k per batch with the next batch's loads in flight.  Once
+// per factor and call: 31 us for two pairs of 256 tiles.
+template <class A, class B>
+__device__ __forceinline__ d4 product64(int k0, int k1, A a, B b) {  // sum over k0 <= k < k1, multiples of 64
+  d4 acc = {0, 0, 0, 0};
+  double va[2][16], vb[2][16];
+  auto load = [&](int s, int kk) {
+    a(kk, va[s]);
+    b(kk, vb[s]);
+  };
+  auto mma = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(va[s][u], vb[s][u], acc, 0, 0, 0);
+  };
+  load(0, k0);
+  for (int kk = k0; kk < k1; kk += 128) {
+    if (kk + 64 < k1) load(1, kk + 64);
+    mma(0);
+    if (kk + 128 < k1) load(0, kk + 128);
+    if (kk + 64 < k1) mma(1);
+  }
+  return acc;
 }
-hipError_t launch_bwd_diag(const TileView& tv, const double* Linv, int k, double* V, double* X, int64_t ld,
-                           int nrhs, double* stage, hipStream_t s) {
-  k_bwd_diag<<<dim3(tv.nb / 16, nchunk(nrhs)), STHREADS, 0, s>>>(tv.nb, Linv, k, V, X, ld, nrhs, tv.info, stage);
-  return hipGetLastError();
+
+__global__ __launch_bounds__(STHREADS) void k_pair_inverse(TileView tv, const double* Linv, double* pair) {
+  if (*tv.info) return;
+  extern __shared__ __attribute__((aligned(16))) double pair_lds[];  // U[m][16 columns], rows of 17
+  const int nb = tv.nb, rb = nb / 16;
+  const int k = 2 * (blockIdx.x / rb), c0 = (blockIdx.x % rb) * 16;
+  const double* Ai = Linv + (int64_t)k * nb * nb;
+  const double* Ci = Ai + (int64_t)nb * nb;
+  double* N = pair + (int64_t)(k / 2) * nb * nb;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = lane >> 4, c = lane & 15;
+  // U[m][col] = sum_k B[m][k] A'[k][col], k >= col
+  auto first = [&](auto tag) {
+    constexpr int F = decltype(tag)::value;
+    const typename RawOf<F>::T* B = (const typename RawOf<F>::T*)tv.tile(k + 1, k);
+    const double mul = tv.tmul(k + 1, k);
+    const double* aj = Ai + (int64_t)q * nb + c0 + c;
+    for (int j = w; j < rb; j += SW) {
+      const typename RawOf<F>::T* bj = B + (int64_t)q * nb + 16 * j + c;
+      const d4 t = product64(
+          c0 / 64 * 64, nb,
+          [&](int kk, double (&v)[16]) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = widen<F>(bj[(int64_t)(kk + 4 * u) * nb], mul);
+          },
+          [&](int kk, double (&v)[16]) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = aj[(int64_t)(kk + 4 * u) * nb];
+          });
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pair_lds[(16 * j + q + 4 * r) * 17 + c] = t[r];
+    }
+  };
+  switch (tv.tfmt(k + 1, k)) {
+    case F64: first(std::integral_constant<int, F64>{}); break;
+    case F32: first(std::integral_constant<int, F32>{}); break;
+    case F16: first(std::integral_constant<int, F16>{}); break;
+    case BF16: first(std::integral_constant<int, BF16>{}); break;
+    default: first(std::integral_constant<int, F8>{});
+  }
+  __syncthreads();
+  // N[row][col] = -sum_m C'[row][m] U[m][col], m <= row; lane group q takes the m 2 q + u % 2 of every eight
+  for (int j = w; j < rb; j += SW) {
+    const double* cj = Ci + (int64_t)(16 * j + c) * nb + 2 * q;
+    const double* uc = pair_lds + 2 * q * 17 + c;
+    const d4 t = product64(
+        0, (16 * j / 64 + 1) * 64,
+        [&](int kk, double (&v)[16]) {
+#pragma unroll
+          for (int u = 0; u < 16; u += 2) {
+            const double2 x = *(const double2*)(cj + kk + 4 * u);
+            v[u] = x.x;
+            v[u + 1] = x.y;
+          }
+        },
+        [&](int kk, double (&v)[16]) {
+#pragma unroll
+          for (int u = 0; u < 16; u += 2) {
+            v[u] = uc[(kk + 4 * u) * 17];
+            v[u + 1] = uc[(kk + 4 * u + 1) * 17];
+          }
+        });
+#pragma unroll
+    for (int r = 0; r < 4; ++r) N[(int64_t)(16 * j + q + 4 * r) * nb + c0 + c] = -t[r];
+  }
 }
-hipError_t launch_bwd_update(const TileView& tv, int k, double* V, const double* stage, int64_t ld, int nrhs,
-                             hipStream_t s) {
-  if (k <= 0) return hipSuccess;
-  if (k >= WIDE_MIN_TILES)
-    k_bwd_update4<<<dim3(k * (tv.nb / 64), nchunk(nrhs)), 64 * SW4, 0, s>>>(tv, k, V, stage, ld, nrhs);
-  else
-    k_bwd_update<<<dim3(k * (tv.nb / 16), nchunk(nrhs)), STHREADS, 0, s>>>(tv, k, V, stage, ld, nrhs);
+
+hipError_t launch_pair_inverse(const TileView& tv, const double* Linv, double* pair, hipStream_t s) {
+  if (tv.nt < 2) return hipSuccess;
+  k_pair_inverse<<<(tv.nt / 2) * (tv.nb / 16), STHREADS, 17 * tv.nb * sizeof(double), s>>>(tv, Linv, pair);
   return hipGetLastError();
 }
 
