@@ -2034,8 +2034,7 @@ int mpcr_mala_run(mpcr_ctx* ctx, int64_t n, const double* d_locs, const mpcr_the
   }
   for (int it = 0; it < iters; ++it) {
     // proposal z' = z - (h/2) M Sigma^-1 z + L_hM eps
-    e = launch_copy_cols((int)n, 1, d_eps + (int64_t)it * n, n, dq, N, s);
-    if (e == hipSuccess) e = launch_trmv_lower(fm->view(), dq, le, s);
+    e = launch_trmv_lower(fm->view(), d_eps + (int64_t)it * n, le, s);
     if (e == hipSuccess) e = launch_axpby((int)n, stz, 1.0, le, zp, s);
     if (e != hipSuccess) return fail(e);
     if ((rc = drift(zp, gzp, stzp)) != MPCR_OK) {

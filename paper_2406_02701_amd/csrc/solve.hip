@@ -909,8 +909,9 @@ hipError_t launch_col_dot(int n, int nrhs, const double* A, const double* B, int
                           double* out, hipStream_t s) {
   int nslab = (n + SLAB - 1) / SLAB;
   if (nslab == 0) nslab = 1;
-  k_col_dot_1<<<dim3(nslab, nrhs), 256, 0, s>>>(n, A, B, ld, partial, nslab);
-  k_col_sum_2<<<(nrhs + 63) / 64, 64, 0, s>>>(nslab, nrhs, partial, out);
+  // (one slab's sum is the result)
+  k_col_dot_1<<<dim3(nslab, nrhs), 256, 0, s>>>(n, A, B, ld, nslab == 1 ? out : partial, nslab);
+  if (nslab > 1) k_col_sum_2<<<(nrhs + 63) / 64, 64, 0, s>>>(nslab, nrhs, partial, out);
   return hipGetLastError();
 }
 
