@@ -255,16 +255,99 @@ k_update_kmajor(TileView tv, int k, const GemmTask* tasks) {
   }
 }
 
+// FP64 updates of a few tiles: one 16 x 16 tile of C per wave (32 x 32 per
+// workgroup), operands straight from memory, 32 k per batch with two batches in
+// flight.  Such a launch lies on the critical path and cannot fill the chip, so
+// what counts is the chain of one wave: nb / 4 dependent MFMAs and few trips to
+// memory, no barriers.  Products are added in ascending k as in k_update_kmajor.
+// Measured, alone, 64 x 64 blocks -> this: one 256 tile 16.2 -> 7.3 us, eight 16.7
+// -> 12.1, sixteen 17.3 -> 20.2; one 512 tile 27.9 -> 11.4, two 28.5 -> 20.2, four
+// 30.1 -> 35.0.
+template <int F>
+__device__ __forceinline__ void load_batch(const char* p, unsigned own, int64_t step, double (&v)[8]) {
+#pragma unroll
+  for (int u = 0; u < 8; ++u) v[u] = load_wide(p + u * step + own, F, 0);
+}
+
+__global__ __launch_bounds__(256, 4) void k_update_direct(TileView tv, int k, const GemmTask* tasks) {
+  const int nb = tv.nb, sub = nb / 32, task = blockIdx.x / (sub * sub), blk = blockIdx.x % (sub * sub);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = lane >> 4, i = lane & 15;
+  const GemmTask t = tasks[task];
+  const int R0 = blk % sub * 32 + 16 * (wave & 1), C0 = blk / sub * 32 + 16 * (wave >> 1);
+  if (t.i == t.j && C0 > R0) return;
+  if (*tv.info) return;
+  __builtin_amdgcn_s_setprio(2);
+  const int fa = __builtin_amdgcn_readfirstlane(tv.tfmt(t.i, k)), fb = __builtin_amdgcn_readfirstlane(tv.tfmt(t.j, k));
+  const double ma = tv.tmul(t.i, k), mb = tv.tmul(t.j, k);
+  // one operand: its rows' first element, the lane's offset and the way from one k4 step to the next, in bytes
+  struct Operand {
+    const char* p;
+    unsigned own;
+    int64_t step;
+  };
+  auto operand = [&](int ti, int f, int row) {
+    const int es = fmt_bytes(f);
+    return Operand{(const char*)tv.tile(ti, k) + row * es, (unsigned)((q * nb + i) * es), (int64_t)4 * nb * es};
+  };
+  Operand a = operand(t.i, fa, R0), b = operand(t.j, fb, C0);
+  auto load = [&](Operand& o, int f, double mul, double (&v)[8]) {
+    switch (f) {
+      case F64: load_batch<F64>(o.p, o.own, o.step, v); break;
+      case F32: load_batch<F32>(o.p, o.own, o.step, v); break;
+      case F16: load_batch<F16>(o.p, o.own, o.step, v); break;
+      case BF16: load_batch<BF16>(o.p, o.own, o.step, v); break;
+      default:
+        load_batch<F8>(o.p, o.own, o.step, v);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] *= mul;
+    }
+    o.p += 8 * o.step;
+  };
+  double* C = (double*)tv.tile(t.i, t.j) + (int64_t)(C0 + q) * nb + R0 + i;
+  double old[4], va[2][8], vb[2][8];
+  d4 acc = {0, 0, 0, 0};
+  load(a, fa, ma, va[0]);
+  load(b, fb, mb, vb[0]);
+  load(a, fa, ma, va[1]);
+  load(b, fb, mb, vb[1]);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) old[r] = C[(int64_t)(4 * r) * nb];
+  auto product = [&](int s) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(vb[s][u], va[s][u], acc, 0, 0, 0);
+  };
+  for (int n = 0; n < nb; n += 64) {
+    const bool more = n + 64 < nb;
+    product(0);
+    if (more) {
+      load(a, fa, ma, va[0]);
+      load(b, fb, mb, vb[0]);
+    }
+    product(1);
+    if (more) {
+      load(a, fa, ma, va[1]);
+      load(b, fb, mb, vb[1]);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) C[(int64_t)(4 * r) * nb] = old[r] - acc[r];
+}
+
 // fewer 128 x 128 blocks than this: 64 x 64 ones (three rounds of two
 // workgroups per CU; measured on either side, see KMajor)
 constexpr int SMALL_UPDATE_MAX = 1536;
+// up to this many 32 x 32 blocks (two per CU): one workgroup each (measured on
+// either side, see k_update_direct)
+constexpr int DIRECT_UPDATE_MAX = 512;
 
 hipError_t launch_tile_update(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks, hipStream_t s) {
   if (ntasks == 0) return hipSuccess;
   const int64_t sub = tv.nb / UBM, blocks = ntasks * sub * sub;
   switch (cfmt) {
     case F64:
-      if (blocks < SMALL_UPDATE_MAX)
+      if (ntasks * (int64_t)(tv.nb / 32) * (tv.nb / 32) <= DIRECT_UPDATE_MAX)
+        k_update_direct<<<(unsigned)(16 * blocks), 256, 0, s>>>(tv, k, tasks);
+      else if (blocks < SMALL_UPDATE_MAX)
         k_update_kmajor<F64, true><<<(unsigned)(4 * blocks), KMajor<F64, true>::NT, 0, s>>>(tv, k, tasks);
       else
         k_update_kmajor<F64, false><<<(unsigned)blocks, KMajor<F64, false>::NT, 0, s>>>(tv, k, tasks);
