@@ -426,6 +426,12 @@ int make_factor(mpcr_ctx* ctx, int64_t n, int64_t nb, const std::vector<uint8_t>
 // it before TRSM(k+1).  Stream U carries the rest of step k's trailing update
 // (columns k+2 ..).  U and C wait for TRSM(k); P and C wait for U's step k-1
 // before they touch column k+1, which that step also updates.
+// Up to LOOKAHEAD_MIN_N (padded order) everything stays on P: the trailing updates
+// are then shorter than what the event packets between the streams cost, which
+// the kernels around them drain for (n = 1024 692 us with lookahead, 615 without;
+// 3072 1850 and 1757 with tiles of 256, 1807 and 1730 with 512; 4096 2577 and 2563;
+// 6000 4360 and 4500).
+constexpr int64_t LOOKAHEAD_MIN_N = 3072;
 constexpr int64_t COL_STREAM_MIN_NT = 32;  // more tiles per dimension than this: next column on its own stream
 
 int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
@@ -438,20 +444,31 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
   // the column stream pays off once the trailing updates are long enough to
   // hide POTRF(k+1) behind; small factorisations (serving) keep the next
   // column on P, which then runs POTRF(k), TRSM(k) and the whole column k+1
-  const bool use_col = nt > COL_STREAM_MIN_NT;
-  HIP_TRY(ctx, ensure_lookahead(ctx, (size_t)(4 * nt + 2), use_col));
+  const bool use_col = nt > COL_STREAM_MIN_NT;  // (tiles are 128 at least: more than LOOKAHEAD_MIN_N)
+  const bool ahead = f->N > LOOKAHEAD_MIN_N;
+  if (ahead) HIP_TRY(ctx, ensure_lookahead(ctx, (size_t)(4 * nt + 2), use_col));
   // the trailing updates of step k go to U (FP64 tiles) and U2 (the other
   // formats): a tile has one format, so the two streams never write the same
   // tile, and their launches fill each other's tails
-  hipStream_t U = ctx->upd, C = use_col ? ctx->col : P, U2 = use_col ? ctx->upd2 : ctx->upd;
-  auto ev = [&](int64_t i) { return ctx->sync_ev[i]; };      // 2k: TRSM(k) done (P), 2k+1: U's step k done
-  auto evc = [&](int64_t k) { return ctx->sync_ev[2 * nt + 2 + k]; };  // C's column k+1 done
-  auto ev2 = [&](int64_t k) { return ctx->sync_ev[3 * nt + 2 + k]; };  // U2's step k done
+  hipStream_t U = ahead ? ctx->upd : P, C = use_col ? ctx->col : P, U2 = use_col ? ctx->upd2 : U;
+  auto ev = [&](int64_t i) { return i; };  // 2k: TRSM(k) done (P), 2k+1: U's step k done
+  auto evc = [&](int64_t k) { return 2 * nt + 2 + k; };      // C's column k+1 done
+  auto ev2 = [&](int64_t k) { return U2 == U ? 2 * k + 1 : 3 * nt + 2 + k; };  // U2's step k done
+  // A stream neither waits for its own events nor records any that it alone waits
+  // for: each is a packet that the kernels around it drain for.
+  std::vector<hipStream_t> owner((size_t)(4 * nt + 2), nullptr);
+  auto record = [&](int64_t e, hipStream_t by, bool others) -> hipError_t {
+    owner[(size_t)e] = by;
+    return ahead && others ? hipEventRecord(ctx->sync_ev[(size_t)e], by) : hipSuccess;
+  };
+  auto wait = [&](hipStream_t on, int64_t e) -> hipError_t {
+    return owner[(size_t)e] == on ? hipSuccess : hipStreamWaitEvent(on, ctx->sync_ev[(size_t)e], 0);
+  };
   // U, U2 and C start after everything queued on P so far (the tile fill)
-  HIP_TRY(ctx, hipEventRecord(ev(2 * nt), P));
-  HIP_TRY(ctx, hipStreamWaitEvent(U, ev(2 * nt), 0));
-  HIP_TRY(ctx, hipStreamWaitEvent(C, ev(2 * nt), 0));
-  if (U2 != U) HIP_TRY(ctx, hipStreamWaitEvent(U2, ev(2 * nt), 0));
+  HIP_TRY(ctx, record(ev(2 * nt), P, true));
+  HIP_TRY(ctx, wait(U, ev(2 * nt)));
+  HIP_TRY(ctx, wait(C, ev(2 * nt)));
+  if (U2 != U) HIP_TRY(ctx, wait(U2, ev(2 * nt)));
   static const int order[5] = {F64, F32, BF16, F16, F8};
   const int64_t nb2 = f->nb * f->nb;
   // FP32 updates through the BF16 MFMA read split panels (two step parities)
@@ -506,7 +523,7 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
     bool fp8_panel = false;
     for (int64_t i = k + 1; i < nt; ++i) fp8_panel |= (f->map[i * nt + k] == F8);
     HIP_TRY(ctx, timed(ctx, P, 5, nb3 / 3.0, [&] { return launch_potrf_tile(tv, (int)k, f->d_dinv + k * f->nb * 32, P); }));
-    if (k > 0) HIP_TRY(ctx, hipStreamWaitEvent(P, evc(k - 1), 0));  // column k updated by C
+    if (k > 0) HIP_TRY(ctx, wait(P, evc(k - 1)));  // column k updated by C
     HIP_TRY(ctx, timed(ctx, P, 6, nb3 * (double)(nt - k - 1),
                        [&] { return launch_trsm_panel(tv, (int)k, f->d_trsm_ws, f->d_dinv + k * f->nb * 32, fp8_panel, P); }));
     if (f->task_cnt[k * 5 + F8] > 0)  // operand scales of the FP8 updates (buffer of this step's parity)
@@ -518,31 +535,31 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
       uint16_t* ob = (pack16 && f->task_cnt[k * 5 + BF16] > 0) ? f->d_b16 + (k & 1) * b16_stride : nullptr;
       HIP_TRY(ctx, launch_pack_split(tv, (int)k, o3, ob, P));
     }
-    HIP_TRY(ctx, hipEventRecord(ev(2 * k), P));
+    HIP_TRY(ctx, record(ev(2 * k), P, true));
     // P next updates the diagonal tile (k+1, k+1), last written by U in step
     // k-1 (diagonal tiles are FP64).  It does not wait for U2: the FP32 and
     // lower tiles of step k-1 matter to P only from TRSM(k+1) on (the panel
     // tiles, and the split-panel buffer that pack(k+1) rewrites), and C, which
     // P waits for before TRSM(k+1), has waited for U2.  POTRF(k+1) thus
     // overlaps the tail of step k-1's lower-format update.
-    if (k > 0) HIP_TRY(ctx, hipStreamWaitEvent(P, ev(2 * (k - 1) + 1), 0));
+    if (k > 0) HIP_TRY(ctx, wait(P, ev(2 * (k - 1) + 1)));
     if ((rc = launch_updates(k, P, 0)) != MPCR_OK) return rc;
-    HIP_TRY(ctx, hipStreamWaitEvent(C, ev(2 * k), 0));
+    HIP_TRY(ctx, wait(C, ev(2 * k)));
     if (k > 0) {
-      HIP_TRY(ctx, hipStreamWaitEvent(C, ev(2 * (k - 1) + 1), 0));
-      HIP_TRY(ctx, hipStreamWaitEvent(C, ev2(k - 1), 0));
+      HIP_TRY(ctx, wait(C, ev(2 * (k - 1) + 1)));
+      HIP_TRY(ctx, wait(C, ev2(k - 1)));
     }
     if ((rc = launch_updates(k, C, 1)) != MPCR_OK) return rc;
-    HIP_TRY(ctx, hipEventRecord(evc(k), C));
-    HIP_TRY(ctx, hipStreamWaitEvent(U, ev(2 * k), 0));
-    if (U2 != U) HIP_TRY(ctx, hipStreamWaitEvent(U2, ev(2 * k), 0));
+    HIP_TRY(ctx, record(evc(k), C, C != P));
+    HIP_TRY(ctx, wait(U, ev(2 * k)));
+    if (U2 != U) HIP_TRY(ctx, wait(U2, ev(2 * k)));
     if ((rc = launch_updates(k, U, 2)) != MPCR_OK) return rc;
-    HIP_TRY(ctx, hipEventRecord(ev(2 * k + 1), U));
-    HIP_TRY(ctx, hipEventRecord(ev2(k), U2));
+    HIP_TRY(ctx, record(ev(2 * k + 1), U, true));
+    if (U2 != U) HIP_TRY(ctx, record(ev2(k), U2, true));
   }
-  HIP_TRY(ctx, hipStreamWaitEvent(P, ev(2 * nt - 1), 0));  // join
-  HIP_TRY(ctx, hipStreamWaitEvent(P, ev2(nt - 1), 0));
-  HIP_TRY(ctx, hipStreamWaitEvent(P, evc(nt - 1), 0));
+  HIP_TRY(ctx, wait(P, ev(2 * nt - 1)));  // join
+  HIP_TRY(ctx, wait(P, ev2(nt - 1)));
+  HIP_TRY(ctx, wait(P, evc(nt - 1)));
   return MPCR_OK;
 }
 
