@@ -486,19 +486,20 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
   if (pack16 && !f->d_b16)
     HIP_TRY(ctx, dmalloc(f->arena, &f->d_b16, (size_t)(2 * b16_stride) * sizeof(uint16_t)));
   // which: 0 = the SYRK of the next diagonal tile, 1 = the rest of the next
-  // column, 2 = the columns after it
+  // column, 2 = the columns after it, 3 = all of them
   auto launch_updates = [&](int64_t k, hipStream_t s0, int which) -> int {
     for (int p : order) {
       const hipStream_t s = (which == 2 && p != F64) ? U2 : s0;
       const int all = f->task_cnt[k * 5 + p], nx = f->task_cnt_next[k * 5 + p];
       // the next column's tasks come first, its diagonal tile (FP64) first among them
       const int nd = (p == F64 && nx > 0) ? 1 : 0;
-      const int off = which == 0 ? 0 : which == 1 ? nd : nx;
-      const int cnt = which == 0 ? nd : which == 1 ? nx - nd : all - nx;
+      const int off = which == 1 ? nd : which == 2 ? nx : 0;
+      const int cnt = which == 0 ? nd : which == 1 ? nx - nd : which == 2 ? all - nx : all;
       if (cnt <= 0) continue;
       const GemmTask* t = f->d_tasks + f->task_off[k * 5 + p] + off;
       // GEMM tiles count 2 nb^3, the SYRK (diagonal) tiles nb^3
-      const double ndiag = (p == F64) ? (which == 0 ? 1.0 : which == 1 ? 0.0 : (double)(nt - k - 2)) : 0.0;
+      const double ndiag =
+          (p == F64) ? (which == 0 ? 1.0 : which == 1 ? 0.0 : (double)(nt - k - (which == 2 ? 2 : 1))) : 0.0;
       const double fl = nb3 * (2.0 * cnt - ndiag);
       if (p == F8) {  // each stream stages in its own part of the FP8 workspace
         const int base = which == 2 ? f->f8_maxP : 0;
@@ -506,6 +507,9 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
         HIP_TRY(ctx, timed(ctx, s, p, fl, [&] {
           return launch_tile_update_fp8(tv, (int)k, t, cnt, pamax, f->d_ws8 + (int64_t)base * nb2, f->d_amax8 + base, s);
         }));
+      } else if (which == 3 && p == F64) {
+        const bool split = nd > 0 && f->map[(k + 1) * nt + k] == F64;
+        HIP_TRY(ctx, timed(ctx, s, p, fl, [&] { return launch_tile_update_direct(tv, (int)k, t, cnt, split, s); }));
       } else if (which == 0 && f->map[(k + 1) * nt + k] == F64) {
         HIP_TRY(ctx, timed(ctx, s, 10, fl, [&] { return launch_syrk_tile(tv, (int)k, (int)k + 1, s); }));
       } else if ((p == F32 && split32) || (p == BF16 && pack16)) {
@@ -543,6 +547,12 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
     // P waits for before TRSM(k+1), has waited for U2.  POTRF(k+1) thus
     // overlaps the tail of step k-1's lower-format update.
     if (k > 0) HIP_TRY(ctx, wait(P, ev(2 * (k - 1) + 1)));
+    if (!ahead && direct_update_fits((int)f->nb, f->task_cnt[k * 5 + F64])) {
+      // one launch for all FP64 tiles of the step
+      if ((rc = launch_updates(k, P, 3)) != MPCR_OK) return rc;
+      for (int64_t e : {evc(k), ev(2 * k + 1)}) HIP_TRY(ctx, record(e, P, false));
+      continue;
+    }
     if ((rc = launch_updates(k, P, 0)) != MPCR_OK) return rc;
     HIP_TRY(ctx, wait(C, ev(2 * k)));
     if (k > 0) {

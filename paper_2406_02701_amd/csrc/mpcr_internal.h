@@ -282,6 +282,11 @@ hipError_t launch_pack_split(const TileView& tv, int k, uint16_t* out3, uint16_t
 // products) or BF16 (one plane)
 hipError_t launch_tile_update_packed(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks,
                                      const uint16_t* planes, hipStream_t s);
+// FP64 tiles, few of them (direct_update_fits); split_first: the first task is a
+// diagonal tile whose contraction is summed in two halves (as launch_syrk_tile)
+bool direct_update_fits(int nb, int ntasks);
+hipError_t launch_tile_update_direct(const TileView& tv, int k, const GemmTask* tasks, int ntasks, bool split_first,
+                                     hipStream_t s);
 hipError_t launch_tile_update(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks, hipStream_t s);
 hipError_t launch_tile_update_16(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks, hipStream_t s);
 hipError_t launch_logdet(const TileView& tv, double* out, hipStream_t s);

@@ -259,17 +259,19 @@ k_update_kmajor(TileView tv, int k, const GemmTask* tasks) {
 // workgroup), operands straight from memory, 32 k per batch with two batches in
 // flight.  Such a launch lies on the critical path and cannot fill the chip, so
 // what counts is the chain of one wave: nb / 4 dependent MFMAs and few trips to
-// memory, no barriers.  Products are added in ascending k as in k_update_kmajor.
+// memory, no barriers.  Products are added in ascending k as in k_update_kmajor;
+// with split_first those of the first task in two halves, as k_syrk_tile does.
 // Measured, alone, 64 x 64 blocks -> this: one 256 tile 16.2 -> 7.3 us, eight 16.7
 // -> 12.1, sixteen 17.3 -> 20.2; one 512 tile 27.9 -> 11.4, two 28.5 -> 20.2, four
 // 30.1 -> 35.0.
+// On one stream a step's FP64 tiles go in one launch (n = 1024 591 -> 568 us).
 template <int F>
 __device__ __forceinline__ void load_batch(const char* p, unsigned own, int64_t step, double (&v)[8]) {
 #pragma unroll
   for (int u = 0; u < 8; ++u) v[u] = load_wide(p + u * step + own, F, 0);
 }
 
-__global__ __launch_bounds__(256, 4) void k_update_direct(TileView tv, int k, const GemmTask* tasks) {
+__global__ __launch_bounds__(256, 4) void k_update_direct(TileView tv, int k, const GemmTask* tasks, int split_first) {
   const int nb = tv.nb, sub = nb / 32, task = blockIdx.x / (sub * sub), blk = blockIdx.x % (sub * sub);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = lane >> 4, i = lane & 15;
   const GemmTask t = tasks[task];
@@ -305,7 +307,8 @@ __global__ __launch_bounds__(256, 4) void k_update_direct(TileView tv, int k, co
   };
   double* C = (double*)tv.tile(t.i, t.j) + (int64_t)(C0 + q) * nb + R0 + i;
   double old[4], va[2][8], vb[2][8];
-  d4 acc = {0, 0, 0, 0};
+  d4 acc = {0, 0, 0, 0}, half = {0, 0, 0, 0};
+  const int mid = split_first && task == 0 ? nb / 2 : nb;
   load(a, fa, ma, va[0]);
   load(b, fb, mb, vb[0]);
   load(a, fa, ma, va[1]);
@@ -318,6 +321,10 @@ __global__ __launch_bounds__(256, 4) void k_update_direct(TileView tv, int k, co
   };
   for (int n = 0; n < nb; n += 64) {
     const bool more = n + 64 < nb;
+    if (n == mid) {
+      half = acc;
+      acc = d4{0, 0, 0, 0};
+    }
     product(0);
     if (more) {
       load(a, fa, ma, va[0]);
@@ -330,7 +337,7 @@ __global__ __launch_bounds__(256, 4) void k_update_direct(TileView tv, int k, co
     }
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) C[(int64_t)(4 * r) * nb] = old[r] - acc[r];
+  for (int r = 0; r < 4; ++r) C[(int64_t)(4 * r) * nb] = old[r] - (mid < nb ? half[r] + acc[r] : acc[r]);
 }
 
 // fewer 128 x 128 blocks than this: 64 x 64 ones (three rounds of two
@@ -340,14 +347,24 @@ constexpr int SMALL_UPDATE_MAX = 1536;
 // either side, see k_update_direct)
 constexpr int DIRECT_UPDATE_MAX = 512;
 
+bool direct_update_fits(int nb, int ntasks) {
+  return ntasks * (int64_t)(nb / 32) * (nb / 32) <= DIRECT_UPDATE_MAX;
+}
+
+hipError_t launch_tile_update_direct(const TileView& tv, int k, const GemmTask* tasks, int ntasks, bool split_first,
+                                     hipStream_t s) {
+  const int sub = tv.nb / 32;
+  k_update_direct<<<(unsigned)(ntasks * sub * sub), 256, 0, s>>>(tv, k, tasks, split_first);
+  return hipGetLastError();
+}
+
 hipError_t launch_tile_update(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks, hipStream_t s) {
   if (ntasks == 0) return hipSuccess;
   const int64_t sub = tv.nb / UBM, blocks = ntasks * sub * sub;
   switch (cfmt) {
     case F64:
-      if (ntasks * (int64_t)(tv.nb / 32) * (tv.nb / 32) <= DIRECT_UPDATE_MAX)
-        k_update_direct<<<(unsigned)(16 * blocks), 256, 0, s>>>(tv, k, tasks);
-      else if (blocks < SMALL_UPDATE_MAX)
+      if (direct_update_fits(tv.nb, ntasks)) return launch_tile_update_direct(tv, k, tasks, ntasks, false, s);
+      if (blocks < SMALL_UPDATE_MAX)
         k_update_kmajor<F64, true><<<(unsigned)(4 * blocks), KMajor<F64, true>::NT, 0, s>>>(tv, k, tasks);
       else
         k_update_kmajor<F64, false><<<(unsigned)blocks, KMajor<F64, false>::NT, 0, s>>>(tv, k, tasks);
