@@ -163,7 +163,7 @@ def measured_traffic(kind, guard):
     if not os.path.exists(path):
         return None
     rec = dict(l.split(": ", 1) for l in open(path).read().splitlines() if ": " in l and not l.startswith(("|", "#")))
-    src = os.path.join(ROOT, "paper_2406_02701_amd", "csrc", "factor.hip")
+    src = os.path.join(ROOT, "paper_2406_02701_amd", "csrc", "update.hip")
     if hashlib.sha256(open(src, "rb").read()).hexdigest() != rec.get("kernel_source_sha256", "").strip():
         return None
     v = rec.get(f"traffic_bytes_per_launch[{kind}@{guard:g}]")

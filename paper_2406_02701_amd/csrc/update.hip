@@ -491,12 +491,12 @@ hipError_t launch_pack_split(const TileView& tv, int k, uint16_t* out3, uint16_t
 
 // Updates from the packed panels of step k (see k_pack_split), planes copied
 // with 16-byte loads (four per row of a chunk).  NPL = 3: FP32 output tiles,
-// the six split products of k_update_f32_split; NPL = 1: BF16 output tiles,
-// one BF16 product per fragment pair on operands rounded once to BF16 (the
-// same k order of MFMAs as k_update_mmajor<BF16>, so the same results).  NW waves per 128 x 128 block: 8 waves of 64 x 32 or
-// 4 waves of 64 x 64; both run at the same rate in the factorisation (about
-// 112 TF/s FP32-equivalent at n = 32768), where the three planes (6 bytes per
-// operand element) make the operand stream, not the LDS or the MFMA, the limit.
+// the six split products; NPL = 1: BF16 output tiles, one BF16 product per
+// fragment pair on operands rounded once to BF16 (the same k order of MFMAs as
+// k_update_mmajor<BF16>, so the same results).  128 x 128 blocks of 8 waves of 64 x
+// 32: the three planes (6 bytes per operand element) make the operand stream, not
+// the LDS or the MFMA, the limit, which is why large FP32 launches take
+// k_update_split_big.
 constexpr int SPLIT_WAVES = 8;
 
 template <int NW, int NPL>
