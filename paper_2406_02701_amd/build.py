@@ -30,11 +30,17 @@ CFLAGS = [
 ]
 # roctx ranges (rocprofiler-sdk)
 LINK_FLAGS = ["-L/opt/rocm/lib", "-lrocprofiler-sdk-roctx"]
-SOURCES = ["tiles.hip", "update.hip", "factor.hip", "panel.hip", "solve.hip", "order.hip", "gemm.hip", "laplace.hip", "mala.hip", "krylov.hip", "api.cpp", "serve.cpp"]
+LD = os.environ.get("LD_LLD", "/opt/rocm/llvm/bin/ld.lld")
+# the factorisation's kernels: three sources compiled side by side (the slowest of
+# the library), joined into the one object factor.o
+FACTOR_PARTS = ["update.hip", "factor.hip", "panel.hip"]
+SOURCES = FACTOR_PARTS + ["tiles.hip", "solve.hip", "order.hip", "gemm.hip", "laplace.hip", "mala.hip",
+                          "krylov.hip", "api.cpp", "serve.cpp"]
 
 
 def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+    stem = os.path.splitext(src)[0]
+    obj = os.path.join(BUILD, stem + (".part.o" if src in FACTOR_PARTS else ".o"))
     cmd = [HIPCC, *CFLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
@@ -45,17 +51,23 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _link(cmd: list) -> None:
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link failed:\n{r.stderr}")
+
+
 def build(jobs: int = 8) -> str:
     if not shutil.which(HIPCC) and not os.path.exists(HIPCC):
         raise RuntimeError("hipcc not found")
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, SOURCES))
+    parts, objs = objs[:len(FACTOR_PARTS)], objs[len(FACTOR_PARTS):]
+    factor = os.path.join(BUILD, "factor.o")
+    _link([LD, "-r", *parts, "-o", factor])
     tmp = LIB + ".tmp"
-    cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, *LINK_FLAGS, "-o", tmp]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stderr}")
+    _link([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", factor, *objs, *LINK_FLAGS, "-o", tmp])
     os.replace(tmp, LIB)
     return LIB
 
