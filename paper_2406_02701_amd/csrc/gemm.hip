@@ -277,17 +277,59 @@ k_gemm(int64_t M, int64_t N, int64_t K, double alpha, const void* Av, int64_t ld
 // column; the same lane-to-k assignment for both operands makes the sum
 // correct for any internal order of the 128 products.
 //
-// Bound: at 8192^3 by LDS reads and the matrix cores together.  Whole calls,
+// Bound: FP8 at 8192^3 by LDS reads and the matrix cores together.  Whole calls,
 // before -> after (kernels for whole shapes only, generic bytewise one for the
 // rest, exponents requested behind the next stage's operands, bounds checks on
 // every store): FP8 TN 8192^3 643 -> 630 us, NN 734 -> 658 us, TN 3001 x 2999 x
-// 4003 560 -> 110 us, NN 2000^3 114 -> 47 us; BF16 NN 8192^3 1200 -> 1136 us,
+// 4003 560 -> 110 us, NN 2000^3 114 -> 47 us; BF16
 // TN 3001 x 2999 x 4003 584 -> 181 us.
 // ---------------------------------------------------------------------------
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int STAGE = 128;  // bytes of k per stage
+constexpr int STAGE = 128;     // bytes of k per stage
+constexpr int LOWP_BIG = 256;  // block of C of k_gemm_lowp_big
+
+// XCD-aware order of the blocks, grouped 8 block rows high (blocks in flight on one XCD share panels)
+__device__ __forceinline__ void lowp_block(int& bi, int& bj) {
+  const int gm = gridDim.x, gn = gridDim.y;
+  const int lb = xcd_remap(blockIdx.y * gm + blockIdx.x, gm * gn);
+  constexpr int GROUP = 8;
+  const int group = lb / (GROUP * gn), first = group * GROUP;
+  const int rows = (gm - first) < GROUP ? (gm - first) : GROUP;
+  bi = first + (lb % (GROUP * gn)) % rows;
+  bj = (lb % (GROUP * gn)) / rows;
+}
+
+// lane (g16, q), register r of tile (a, b): C[R0 + 16 a][C0 + 16 b + r], R0 and C0 the lane's first row and column
+template <int TA, int TB>
+__device__ __forceinline__ void lowp_store(const f4 (&acc)[TA][TB], double alpha, double beta, void* Cv, int64_t ldc,
+                                           int cprec, int64_t R0, int64_t C0, int64_t M, int64_t N, bool whole_block) {
+  auto write = [&](auto* Cp, auto whole) {
+    using T = std::remove_pointer_t<decltype(Cp)>;
+    Cp += C0 * ldc + R0;
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        T* col = Cp + (b * 16 + r) * ldc;
+#pragma unroll
+        for (int a = 0; a < TA; ++a) {
+          if (!decltype(whole)::value && (R0 + a * 16 >= M || C0 + b * 16 + r >= N)) continue;
+          double v = alpha * (double)acc[a][b][r];
+          if (beta != 0.0) v += beta * (double)col[a * 16];
+          col[a * 16] = (T)v;
+        }
+      }
+  };
+  if (cprec == F64) {
+    if (whole_block) write((double*)Cv, std::true_type{});
+    else write((double*)Cv, std::false_type{});
+  } else {
+    if (whole_block) write((float*)Cv, std::true_type{});
+    else write((float*)Cv, std::false_type{});
+  }
+}
 
 template <int P, int WM, int WN, int TA, int TB, int PAD>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N, int64_t K, double alpha,
@@ -304,13 +346,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
   constexpr int LDR = STAGE + PAD;                 // LDS row
   __shared__ __attribute__((aligned(16))) uint8_t As[2][BM * LDR];
   __shared__ __attribute__((aligned(16))) uint8_t Bs[2][BN * LDR];
-  // XCD-aware order, grouped 8 block rows high (blocks in flight on one XCD share panels)
-  const int gm = gridDim.x, gn = gridDim.y;
-  const int lb = xcd_remap(blockIdx.y * gm + blockIdx.x, gm * gn);
-  constexpr int GROUP = 8;
-  const int group = lb / (GROUP * gn), first = group * GROUP;
-  const int rows = (gm - first) < GROUP ? (gm - first) : GROUP;
-  const int bi = first + (lb % (GROUP * gn)) % rows, bj = (lb % (GROUP * gn)) / rows;
+  int bi, bj;
+  lowp_block(bi, bj);
   const int64_t r0 = (int64_t)bi * BM, c0 = (int64_t)bj * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WM, wn = wave / WM;
@@ -446,33 +483,124 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
     }
   }
 
-  // lane (g16, q), register r of tile (a, b): C[r0 + 16 (TA wm + a) + g16][c0 + 16 (TB wn + b) + 4 q + r]
-  const int64_t R0 = r0 + wm * TA * 16 + g16, C0 = c0 + wn * TB * 16 + 4 * q;
-  auto write = [&](auto* Cp, auto whole) {
-    using T = std::remove_pointer_t<decltype(Cp)>;
-    Cp += C0 * ldc + R0;
+  lowp_store<TA, TB>(acc, alpha, beta, Cv, ldc, cprec, r0 + wm * TA * 16 + g16, c0 + wn * TB * 16 + 4 * q, M, N,
+                     r0 + BM <= M && c0 + BN <= N);
+}
+
+// The 16-bit product on 256 x 256 blocks: four waves of 128 x 128, one per SIMD,
+// 256 accumulation registers each.  The MFMAs of a 32-wide k step take 1024
+// cycles of a CU.  With eight waves of 128 x 64 its fragment reads (96 KB) and
+// stores (32 KB, through registers) took as many cycles of the LDS: 45% MFMA
+// busy; here the reads are 64 KB, and the operands go global -> LDS directly.
+// A wave has no other one to hide behind, so nothing it waits for is recent:
+//   - a step's fragments are read, two per eight MFMAs, during the step before it;
+//   - the barrier stands between a stage's two steps: by then the stage's last
+//     fragments are in registers, so the second step reads the next stage's first
+//     ones and the copies of the stage after next go into the buffer given up.
+// A copy of 1 KB is 8 rows of 128 bytes; granule c of row r is kept at c ^ (r % 8),
+// so that the 16 rows of a fragment read spread over the banks.  Every element
+// takes its products in the order of the 128 x 128 blocks: the same bits.
+// Whole calls, before (eight waves) -> after: BF16 NN 8192^3 1122 -> 925 us,
+// TN 1154 -> 935, FP16 1148 -> 947, BF16 4096^3 151 -> 117, 16384 x 4096 x 2048
+// 321 -> 266.  An FP8 form (two sets of eight 32-byte fragments) spills: 2349 us
+// for 612.
+template <int P>
+__global__ __launch_bounds__(256) void k_gemm_lowp_big(int64_t M, int64_t N, int64_t K, double alpha, const void* ATv,
+                                                       int64_t ldat, const void* Bv, int64_t ldb, double beta,
+                                                       void* Cv, int64_t ldc, int cprec) {
+  constexpr int BM = LOWP_BIG, TA = 8, WM = 2, NI = BM / 8 / 4;  // NI copies of 8 rows per wave and operand
+  constexpr int OP = BM * STAGE;                                 // bytes of an operand's stage
+  __shared__ __attribute__((aligned(1024))) uint8_t sm[2][2 * OP];
+  int bi, bj;
+  lowp_block(bi, bj);
+  const int64_t r0 = (int64_t)bi * BM, c0 = (int64_t)bj * BM;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave % WM, wn = wave / WM;
+  const int g16 = lane & 15, q = lane >> 4;
+
+  const int64_t ra = r0 + 64 * wave < M ? r0 + 64 * wave : M - 1, rb = c0 + 64 * wave < N ? c0 + 64 * wave : N - 1;
+  const uint8_t* Ap = (const uint8_t*)ATv + ra * ldat * 2;
+  const uint8_t* Bp = (const uint8_t*)Bv + rb * ldb * 2;
+  uint32_t oa[NI], ob[NI];
 #pragma unroll
-    for (int b = 0; b < TB; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        T* col = Cp + (b * 16 + r) * ldc;
-#pragma unroll
-        for (int a = 0; a < TA; ++a) {
-          if (!decltype(whole)::value && (R0 + a * 16 >= M || C0 + b * 16 + r >= N)) continue;
-          double v = alpha * (double)acc[a][b][r];
-          if (beta != 0.0) v += beta * (double)col[a * 16];
-          col[a * 16] = (T)v;
-        }
-      }
-  };
-  const bool whole = r0 + BM <= M && c0 + BN <= N;
-  if (cprec == F64) {
-    if (whole) write((double*)Cv, std::true_type{});
-    else write((double*)Cv, std::false_type{});
-  } else {
-    if (whole) write((float*)Cv, std::true_type{});
-    else write((float*)Cv, std::false_type{});
+  for (int i = 0; i < NI; ++i) {
+    const int r = 8 * i + (lane >> 3), ch = ((lane & 7) ^ (r & 7)) * 16;
+    oa[i] = (uint32_t)((ra + r < M ? r : M - 1 - ra) * ldat * 2) + ch;
+    ob[i] = (uint32_t)((rb + r < N ? r : N - 1 - rb) * ldb * 2) + ch;
   }
+  const uint32_t lds0 = lds_addr(&sm[0][0]) + wave * NI * 1024;
+  auto issue = [&](int64_t t, int buf, int i) {
+    const uint32_t l = lds0 + buf * 2 * OP + i * 1024;
+    copy16_to_lds(Ap + t * STAGE, oa[i], l);
+    copy16_to_lds(Bp + t * STAGE, ob[i], l + OP);
+  };
+
+  f4 acc[TA][TA];
+#pragma unroll
+  for (int a = 0; a < TA; ++a)
+#pragma unroll
+    for (int b = 0; b < TA; ++b) acc[a][b] = f4{0, 0, 0, 0};
+  u16x8 fa0[TA], fb0[TA], fa1[TA], fb1[TA];
+  int fo[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) fo[h] = g16 * STAGE + (((4 * h + q) ^ (g16 & 7)) * 16);
+  auto frag = [&](int buf, int h, int i, u16x8* fa, u16x8* fb) {
+    fb[i] = *(const u16x8*)(&sm[buf][OP + wn * TA * 16 * STAGE + fo[h]] + i * 16 * STAGE);
+    fa[i] = *(const u16x8*)(&sm[buf][wm * TA * 16 * STAGE + fo[h]] + i * 16 * STAGE);
+  };
+  auto mma = [&](int a, const u16x8* fa, const u16x8* fb) {
+#pragma unroll
+    for (int b = 0; b < TA; ++b) {
+      if constexpr (P == BF16)
+        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fb[b]),
+                                                             __builtin_bit_cast(bf16x8, fa[a]), acc[a][b], 0, 0, 0);
+      else
+        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fb[b]),
+                                                            __builtin_bit_cast(f16x8, fa[a]), acc[a][b], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int64_t stages = K * 2 / STAGE;
+  if (stages > 0) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) issue(0, 0, i);
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" : : : "memory");
+#pragma unroll
+    for (int i = 0; i < TA; ++i) frag(0, 0, i, fa0, fb0);
+    if (stages > 1) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) issue(1, 1, i);
+    }
+    auto stage = [&](int64_t t, int buf, auto more) {
+#pragma unroll
+      for (int a = 0; a < TA; ++a)
+#pragma unroll
+        for (int b = 0; b < TA; ++b) asm volatile("" : "+a"(acc[a][b]));
+#pragma unroll
+      for (int i = 0; i < TA; ++i) {
+        frag(buf, 1, i, fa1, fb1);
+        mma(i, fa0, fb0);
+      }
+      // this stage's last reads are done and the next one's copies are in
+      asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+      wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" : : : "memory");
+#pragma unroll
+      for (int i = 0; i < TA; ++i) {
+        frag(buf ^ 1, 0, i, fa0, fb0);
+        if (decltype(more)::value) issue(t + 2, buf, i);
+        mma(i, fa1, fb1);
+      }
+    };
+    int64_t t = 0;
+    for (; t + 2 < stages; ++t) stage(t, t & 1, std::true_type{});
+    for (; t < stages; ++t) stage(t, t & 1, std::false_type{});
+  }
+  lowp_store<TA, TA>(acc, alpha, beta, Cv, ldc, cprec, r0 + wm * TA * 16 + g16, c0 + wn * TA * 16 + 4 * q, M, N,
+                     r0 + BM <= M && c0 + BM <= N);
 }
 
 // Packs a rows x cols operand into a k-contiguous array: out[r * ldo + c] =
@@ -530,10 +658,13 @@ hipError_t launch_pack(int es, int trans, int64_t rows, int64_t cols, const void
   return hipGetLastError();
 }
 
-// 256 x 256 blocks (eight waves of 128 x 64, half the LDS traffic per product
-// of the 128 x 128 ones) once they fill the chip; a launch that leaves more
-// than a fifth of its last round of 256 CUs idle runs 128 x 128 blocks (four
-// waves of 64 x 64, two workgroups per CU).
+// 256 x 256 blocks (half the LDS traffic per product of the 128 x 128 ones; BF16
+// and FP16: k_gemm_lowp_big, FP8: eight waves of 128 x 64) once they fill the
+// chip; a launch that leaves more than a fifth of its last round of 256 CUs idle
+// runs 128 x 128 blocks (four waves of 64 x 64, two workgroups per CU): n = 2900
+// has 144 blocks of 256 for 256 CUs.  k_gemm_lowp_big's copies hold 63 rows of an
+// operand in a 32-bit offset.
+constexpr int64_t LOWP_BIG_LD = INT64_C(1) << 25;
 static bool large_blocks(int64_t m, int64_t n) {
   const int64_t blocks = ((m + 255) / 256) * ((n + 255) / 256), rounds = (blocks + 255) / 256;
   return blocks * 5 >= rounds * 256 * 4;
@@ -555,13 +686,12 @@ hipError_t launch_gemm_lowp(int prec, int64_t m, int64_t n, int64_t k, double al
       <<<dim3((unsigned)((m + 16 * TA * WM - 1) / (16 * TA * WM)), (unsigned)((n + 16 * TB * WN - 1) / (16 * TB * WN))), \
          64 * WM * WN, 0, s>>>(m, n, k, alpha, AT, ldat, sA, mbA, sa_kmajor, B, ldb, sB, mbB, sb_kmajor, beta, C, ldc, \
                                cprec)
-  if (large_blocks(m, n)) {
-    switch (prec) {
-      case BF16: MPCR_LOWP(BF16, 2, 4, 8, 4, 32); break;
-      case F16: MPCR_LOWP(F16, 2, 4, 8, 4, 32); break;
-      case F8: MPCR_LOWP(F8, 2, 4, 8, 4, 16); break;
-      default: return hipErrorInvalidValue;
-    }
+  if (large_blocks(m, n) && prec != F8 && (ldat > ldb ? ldat : ldb) <= LOWP_BIG_LD) {
+    const dim3 grid((unsigned)((m + LOWP_BIG - 1) / LOWP_BIG), (unsigned)((n + LOWP_BIG - 1) / LOWP_BIG));
+    if (prec == BF16) k_gemm_lowp_big<BF16><<<grid, 256, 0, s>>>(m, n, k, alpha, AT, ldat, B, ldb, beta, C, ldc, cprec);
+    else k_gemm_lowp_big<F16><<<grid, 256, 0, s>>>(m, n, k, alpha, AT, ldat, B, ldb, beta, C, ldc, cprec);
+  } else if (large_blocks(m, n) && prec == F8) {
+    MPCR_LOWP(F8, 2, 4, 8, 4, 16);
   } else {
     switch (prec) {
       case BF16: MPCR_LOWP(BF16, 2, 2, 4, 4, 16); break;

@@ -195,3 +195,10 @@ def test_gemm_sizes_and_alignments(g, fmt, tA, tB, m, n, k, pad, shift):
 @pytest.mark.parametrize("tA,tB", [(False, False), (True, True)])
 def test_gemm_large_block_edges(g, fmt, tA, tB):
     gemm_exact(*g, fmt, 4093, 4090, 37, tA, tB, 0.0, 0, 0)
+
+
+# the 256 x 256 blocks of the 16/8-bit kernels: one to five stages of k, ragged rows and columns
+@pytest.mark.parametrize("fmt", ["fp16", "bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("k", [1, 65, 130, 256, 513])
+def test_gemm_large_block_stages(g, fmt, k):
+    gemm_exact(*g, fmt, 3501, 3900, k, True, k % 2 == 1, 1.0, 0, 0)
