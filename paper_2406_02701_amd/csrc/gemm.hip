@@ -282,7 +282,7 @@ k_gemm(int64_t M, int64_t N, int64_t K, double alpha, const void* Av, int64_t ld
 // rest, exponents requested behind the next stage's operands, bounds checks on
 // every store): FP8 TN 8192^3 643 -> 630 us, NN 734 -> 658 us, TN 3001 x 2999 x
 // 4003 560 -> 110 us, NN 2000^3 114 -> 47 us; BF16
-// TN 3001 x 2999 x 4003 584 -> 181 us.
+// TN 3001 x 2999 x 4003 584 -> 127 us.
 // ---------------------------------------------------------------------------
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -658,16 +658,25 @@ hipError_t launch_pack(int es, int trans, int64_t rows, int64_t cols, const void
   return hipGetLastError();
 }
 
-// 256 x 256 blocks (half the LDS traffic per product of the 128 x 128 ones; BF16
-// and FP16: k_gemm_lowp_big, FP8: eight waves of 128 x 64) once they fill the
-// chip; a launch that leaves more than a fifth of its last round of 256 CUs idle
-// runs 128 x 128 blocks (four waves of 64 x 64, two workgroups per CU): n = 2900
-// has 144 blocks of 256 for 256 CUs.  k_gemm_lowp_big's copies hold 63 rows of an
-// operand in a 32-bit offset.
-constexpr int64_t LOWP_BIG_LD = INT64_C(1) << 25;
+// 256 x 256 blocks (half the LDS traffic per product of the 128 x 128 ones; eight
+// waves of 128 x 64) once they fill the chip; a launch that leaves more than a
+// fifth of its last round of 256 CUs idle runs 128 x 128 blocks (four waves of 64 x
+// 64, two workgroups per CU).
 static bool large_blocks(int64_t m, int64_t n) {
   const int64_t blocks = ((m + 255) / 256) * ((n + 255) / 256), rounds = (blocks + 255) / 256;
   return blocks * 5 >= rounds * 256 * 4;
+}
+
+// BF16, FP16: a round of 256 blocks of k_gemm_lowp_big takes as long as one of 512
+// small blocks (n = 2816, 121 and 484 of them: 76 and 83 us) and brings twice the
+// products, so it is taken where the small ones need a second round (n = 3072: 81
+// and 128 us; 4100: 219 and 276; 5120: 229 and 383; 5888: 379 and 548; small ones
+// 23 and big ones 27 us at 2816 x 2816 x 128).  Its one wave per SIMD starts and
+// ends with nothing beside it, which pays from k = 512 (8192 x 8192 x 1024: 152 us,
+// eight waves 167; x 512: 110 and 111; x 256: 90 and 81; x 64: 69 and 63).  Its
+// copies hold 63 rows of an operand in a 32-bit offset.
+static bool big_blocks(int prec, int64_t m, int64_t n, int64_t k, int64_t ld) {
+  return prec != F8 && ((m + 127) / 128) * ((n + 127) / 128) > 512 && k >= 512 && ld <= (INT64_C(1) << 25);
 }
 
 // k per stage of the 16/8-bit product: its operands' k is a multiple of it
@@ -686,12 +695,17 @@ hipError_t launch_gemm_lowp(int prec, int64_t m, int64_t n, int64_t k, double al
       <<<dim3((unsigned)((m + 16 * TA * WM - 1) / (16 * TA * WM)), (unsigned)((n + 16 * TB * WN - 1) / (16 * TB * WN))), \
          64 * WM * WN, 0, s>>>(m, n, k, alpha, AT, ldat, sA, mbA, sa_kmajor, B, ldb, sB, mbB, sb_kmajor, beta, C, ldc, \
                                cprec)
-  if (large_blocks(m, n) && prec != F8 && (ldat > ldb ? ldat : ldb) <= LOWP_BIG_LD) {
+  if (big_blocks(prec, m, n, k, ldat > ldb ? ldat : ldb)) {
     const dim3 grid((unsigned)((m + LOWP_BIG - 1) / LOWP_BIG), (unsigned)((n + LOWP_BIG - 1) / LOWP_BIG));
     if (prec == BF16) k_gemm_lowp_big<BF16><<<grid, 256, 0, s>>>(m, n, k, alpha, AT, ldat, B, ldb, beta, C, ldc, cprec);
     else k_gemm_lowp_big<F16><<<grid, 256, 0, s>>>(m, n, k, alpha, AT, ldat, B, ldb, beta, C, ldc, cprec);
-  } else if (large_blocks(m, n) && prec == F8) {
-    MPCR_LOWP(F8, 2, 4, 8, 4, 16);
+  } else if (large_blocks(m, n)) {
+    switch (prec) {
+      case BF16: MPCR_LOWP(BF16, 2, 4, 8, 4, 32); break;
+      case F16: MPCR_LOWP(F16, 2, 4, 8, 4, 32); break;
+      case F8: MPCR_LOWP(F8, 2, 4, 8, 4, 16); break;
+      default: return hipErrorInvalidValue;
+    }
   } else {
     switch (prec) {
       case BF16: MPCR_LOWP(BF16, 2, 2, 4, 4, 16); break;

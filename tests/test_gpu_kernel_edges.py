@@ -197,8 +197,9 @@ def test_gemm_large_block_edges(g, fmt, tA, tB):
     gemm_exact(*g, fmt, 4093, 4090, 37, tA, tB, 0.0, 0, 0)
 
 
-# the 256 x 256 blocks of the 16/8-bit kernels: one to five stages of k, ragged rows and columns
+# the 256 x 256 blocks of the 16/8-bit kernels, ragged rows and columns: one to five stages of k, and the k from
+# which a wave takes 128 x 128 (an even and an odd number of stages)
 @pytest.mark.parametrize("fmt", ["fp16", "bf16", "fp8_e4m3"])
-@pytest.mark.parametrize("k", [1, 65, 130, 256, 513])
+@pytest.mark.parametrize("k", [1, 65, 130, 256, 449, 512, 513])
 def test_gemm_large_block_stages(g, fmt, k):
     gemm_exact(*g, fmt, 3501, 3900, k, True, k % 2 == 1, 1.0, 0, 0)
