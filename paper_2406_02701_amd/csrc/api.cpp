@@ -97,6 +97,8 @@ struct mpcr_ctx {
   uint8_t* ws_gemm = nullptr;     // packed 16/8-bit GEMM operands
   uint64_t* noalloc_keys = nullptr;  // device address of the static sort-key array on this device
   int64_t ws_gemm_bytes = 0;
+  double* ws_pair = nullptr;      // inverted pairs of a caller's factor (see tile_solve)
+  int64_t ws_pair_bytes = 0;
   hipEvent_t ev[6] = {};
   // kernel timing (see mpcr_ctx_set_profiling)
   bool profiling = false;
@@ -603,15 +605,17 @@ struct SolveBufs {
   double *scal = nullptr;  // small per-column scalars
   double *partial = nullptr;
   int* active = nullptr;
-  // factors solved with in this call (as of which factorisation), and whether
-  // their pairs of diagonal tiles have been inverted (into the workspace of their
-  // panel solves)
+  // factors solved with in this call (as of which factorisation), and the
+  // inverted pairs of their diagonal tiles, once formed
   struct Solved {
     const mpcr_factor* f;
     int64_t version;
-    bool pairs;
+    const double* pairs;
   };
   std::vector<Solved> solved;
+  // The call's factors are the caller's: other contexts may solve with them at the
+  // same time, so nothing of theirs is written but the context's workspace.
+  bool shared = false;
 };
 
 int64_t solve_bytes(int64_t N, int64_t nrhs, int64_t n) {
@@ -653,6 +657,27 @@ int carve(mpcr_ctx* ctx, int64_t N, int64_t nrhs, int64_t n, SolveBufs& b) {
 // tiles of 512: 131 -> 134 ms), and k_pair_inverse keeps nb x 17 doubles in LDS.
 constexpr int64_t PAIR_NT_MAX = 32, PAIR_NB_MAX = 1024;
 
+// Room for the inverted pairs of f's diagonal tiles: the workspace of its panel
+// solves if f belongs to this call or context, else the context's own.  NULL if the
+// device has none left: the sweeps then go on by single tiles.
+double* pair_space(mpcr_ctx* ctx, mpcr_factor* f, const SolveBufs& b) {
+  if (!b.shared) return f->d_trsm_ws;
+  const int64_t need = f->nt / 2 * f->nb * f->nb * 8;
+  if (ctx->ws_pair_bytes < need) {
+    (void)hipStreamSynchronize(ctx->stream);
+    dfree(ctx->arena, ctx->ws_pair);
+    ctx->ws_pair = nullptr;
+    ctx->ws_pair_bytes = 0;
+    if (dmalloc(ctx->arena, &ctx->ws_pair, (size_t)need) != hipSuccess) {
+      (void)hipGetLastError();  // (or the next launch would report it)
+      ctx->ws_pair = nullptr;
+      return nullptr;
+    }
+    ctx->ws_pair_bytes = need;
+  }
+  return ctx->ws_pair;
+}
+
 // X = M^{-1} B with M = L L^T over the tiles; also leaves W = L^{-1} B.
 int tile_solve(mpcr_ctx* ctx, mpcr_factor* f, SolveBufs& b, const double* Bsrc, double* Xdst, double* Wdst,
                bool backward = true) {
@@ -660,20 +685,23 @@ int tile_solve(mpcr_ctx* ctx, mpcr_factor* f, SolveBufs& b, const double* Bsrc, 
   TileView tv = f->view();
   const int nrhs = (int)b.nrhs;
   const int64_t ld = b.N;
-  // From the second solve with a factor on the sweeps go by pairs of tiles.  The
-  // calls know nothing of each other (they may run on several streams): each
-  // forms the pairs for itself.
+  // From the second solve with a factor on the sweeps go by pairs of tiles, which
+  // every call forms for itself (so a solve's last bits depend on whether it is the
+  // first of its call).
   const double* pair = nullptr;
   if (f->nt > 1 && f->nt <= PAIR_NT_MAX && f->nb <= PAIR_NB_MAX) {
     auto it = std::find_if(b.solved.begin(), b.solved.end(), [&](auto& x) { return x.f == f; });
     if (it == b.solved.end()) {
-      b.solved.push_back({f, f->version, false});
+      b.solved.push_back({f, f->version, nullptr});
     } else if (it->version != f->version) {
-      *it = {f, f->version, false};
+      *it = {f, f->version, nullptr};
     } else {
-      if (!it->pairs) HIP_TRY(ctx, launch_pair_inverse(tv, f->d_Linv, f->d_trsm_ws, s));
-      it->pairs = true;
-      pair = f->d_trsm_ws;
+      if (!it->pairs)
+        if (double* room = pair_space(ctx, f, b)) {
+          HIP_TRY(ctx, launch_pair_inverse(tv, f->d_Linv, room, s));
+          it->pairs = room;
+        }
+      pair = it->pairs;
     }
   }
   // algorithmic flops: 2 N^2 nrhs per triangular sweep
@@ -1244,6 +1272,7 @@ int mpcr_ctx_destroy(mpcr_ctx* ctx) {
     dfree(ctx->arena, ctx->ws_vec);
     dfree(ctx->arena, ctx->ws_kry);
     dfree(ctx->arena, ctx->ws_gemm);
+    dfree(ctx->arena, ctx->ws_pair);
     for (auto& e : ctx->ev) (void)hipEventDestroy(e);
     drain_timing(ctx);
     for (auto& e : ctx->ev_pool) (void)hipEventDestroy(e);
@@ -1524,6 +1553,7 @@ int mpcr_trsm_forward(mpcr_ctx* ctx, const mpcr_factor* fc, int64_t nrhs, const 
   int rc = ensure_linv(ctx, f);
   if (rc) return rc;
   SolveBufs b;
+  b.shared = true;
   if ((rc = carve(ctx, f->N, nrhs, f->n, b)) != MPCR_OK) return rc;
   HIP_TRY(ctx, launch_copy_cols((int)f->n, (int)nrhs, d_B, ldb, b.B, b.N, ctx->stream));
   if ((rc = tile_solve(ctx, f, b, b.B, b.X, b.W, false)) != MPCR_OK) return rc;
@@ -1552,6 +1582,7 @@ int mpcr_potrs(mpcr_ctx* ctx, const mpcr_factor* fc, int64_t nrhs, const double*
   int rc = ensure_linv(ctx, f);
   if (rc) return rc;
   SolveBufs b;
+  b.shared = true;
   if ((rc = carve(ctx, f->N, nrhs, f->n, b)) != MPCR_OK) return rc;
   HIP_TRY(ctx, launch_copy_cols((int)f->n, (int)nrhs, d_B, ldb, b.B, b.N, s));
   bool conv = true;
