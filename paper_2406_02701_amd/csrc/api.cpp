@@ -610,6 +610,7 @@ struct SolveBufs {
   struct Solved {
     const mpcr_factor* f;
     int64_t version;
+    int64_t solves;
     const double* pairs;
   };
   std::vector<Solved> solved;
@@ -653,9 +654,24 @@ int carve(mpcr_ctx* ctx, int64_t N, int64_t nrhs, int64_t n, SolveBufs& b) {
 }
 
 // Sweeps by pairs of tiles: as long as launches, not the tiles' bytes, bound the
-// steps (n = 7919, 31 tiles of 256: 9.6 -> 9.3 ms for three solves; n = 32768, 64
-// tiles of 512: 131 -> 134 ms), and k_pair_inverse keeps nb x 17 doubles in LDS.
+// steps: up to 32 tiles, where every size gains (31 tiles of 256, eleven solves 9.7
+// -> 8.0 ms; beyond, 36 tiles of 256 still do, 11.9 -> 9.8 ms, but 64 tiles of 512
+// lose, 131 -> 134 ms a likelihood); k_pair_inverse keeps nb x 17 doubles in LDS.
 constexpr int64_t PAIR_NT_MAX = 32, PAIR_NB_MAX = 1024;
+// The solves of a call that go by single tiles before the pairs are formed.  Forming
+// them costs what a pair saves in the solves of
+//   nb 128    2 tiles 0.7
+//   nb 256    2 tiles 1.7   4 tiles 1.1   8 tiles 0.6
+//   nb 512    2 tiles 4.1   4 tiles 2.9   8 tiles 2.3   16 tiles 1.1
+//   nb 640    2 tiles 4.8   4 tiles 3.4   7 tiles 3.1   12 tiles 1.5
+//   nb 1024   2 tiles 9     4 tiles 7.5   9 tiles 5.6
+// and how many are to come is not known.  So about as many go before (the next ones
+// are then likely to be worth it, and a call that stops there has lost little), by a
+// formula that is near these: two solves with 2 tiles of 1024 take 0.28 ms (with pairs
+// from the second on 0.57), eleven with 4 tiles of 256 1.11 ms (1.38 without pairs).
+constexpr int64_t pair_wait(int64_t nb, int64_t nt) {
+  return std::max<int64_t>(1, (nb / 128) * (nb / 128) / (nt + 2));
+}
 
 // Room for the inverted pairs of f's diagonal tiles: the workspace of its panel
 // solves if f belongs to this call or context, else the context's own.  NULL if the
@@ -685,17 +701,15 @@ int tile_solve(mpcr_ctx* ctx, mpcr_factor* f, SolveBufs& b, const double* Bsrc, 
   TileView tv = f->view();
   const int nrhs = (int)b.nrhs;
   const int64_t ld = b.N;
-  // From the second solve with a factor on the sweeps go by pairs of tiles, which
-  // every call forms for itself (so a solve's last bits depend on whether it is the
-  // first of its call).
+  // From some solve with a factor on (pair_wait) the sweeps go by pairs of tiles,
+  // which every call forms for itself; so a solve's last bits depend on its place in
+  // the call.
   const double* pair = nullptr;
   if (f->nt > 1 && f->nt <= PAIR_NT_MAX && f->nb <= PAIR_NB_MAX) {
     auto it = std::find_if(b.solved.begin(), b.solved.end(), [&](auto& x) { return x.f == f; });
-    if (it == b.solved.end()) {
-      b.solved.push_back({f, f->version, nullptr});
-    } else if (it->version != f->version) {
-      *it = {f, f->version, nullptr};
-    } else {
+    if (it == b.solved.end()) it = b.solved.insert(it, {f, f->version, 0, nullptr});
+    if (it->version != f->version) *it = {f, f->version, 0, nullptr};
+    if (it->solves++ >= pair_wait(f->nb, f->nt)) {
       if (!it->pairs)
         if (double* room = pair_space(ctx, f, b)) {
           HIP_TRY(ctx, launch_pair_inverse(tv, f->d_Linv, room, s));

@@ -8,8 +8,8 @@
 // The steps k go by tiles, or by pairs of tiles: then a step's Linv_k is the inverse
 // of the 2 x 2 tile block [[A, 0], [B, C]] on the diagonal, [[A', 0], [-C' B A',
 // C']], whose third tile k_pair_inverse forms.  A step costs two launches on the
-// critical path whatever its width, so pairs pay from the second solve with a
-// factor on.
+// critical path whatever its width, so pairs pay once a call solves often enough with
+// a factor.
 // Off-diagonal tiles are read in their storage format and widened to FP64.
 // All right-hand-side blocks are column-major with leading dimension ld >= the
 // padded order nt*nb; padded rows are kept at zero.
@@ -415,7 +415,8 @@ hipError_t launch_sweep(const TileView& tv, bool forward, const double* Linv, co
 // elements at a time, then -C' U; waves take 16-row tiles in turn.  C' and A' are
 // lower triangular: their zeros are left out by 64-wide blocks.  FP64 MFMA, operands
 // straight from memory, 64 k per batch with the next batch's loads in flight.  Once
-// per factor and call: 31 us for two pairs of 256 tiles.
+// per factor and call: 31 us for two pairs of 256 tiles, about 100 for tiles of 512,
+// 340 for 1024 (a wave goes through nb / 128 tile rows one after the other).
 template <class A, class B>
 __device__ __forceinline__ d4 product64(int k0, int k1, A a, B b) {  // sum over k0 <= k < k1, multiples of 64
   d4 acc = {0, 0, 0, 0};

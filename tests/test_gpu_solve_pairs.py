@@ -90,3 +90,21 @@ def test_one_factor_in_two_contexts(g):
         assert len(got[i]) == 5
         for x in got[i]:
             assert np.array_equal(x, alone[i])
+
+
+# tiles of 256 and more, an even and an odd number of them, as many solves as lead to the pairs of each and
+# two more: the last iterate's residual is that of a refined solve (an iterate x + M^-1 r is rounded to
+# u |x|, and FP32 tiles leave M within 2^-20 of A: after two steps the error is below 1e-12)
+@pytest.mark.parametrize("nb,n,solves", [(256, 512, 5), (256, 768, 4), (512, 1024, 11), (512, 1500, 8), (640, 1280, 15),
+                                         (640, 1800, 11), (1024, 2048, 35), (1024, 3000, 24)])
+@pytest.mark.parametrize("nrhs", [1, 17])
+def test_large_tiles(g, nb, n, solves, nrhs):
+    gu, ctx = g
+    from paper_2406_02701_amd import mpcr
+    A = spd(n)
+    dA, f = factor(gu, ctx, A, nb, 1)
+    B = np.random.default_rng(n).standard_normal((n, nrhs))
+    X = refined(gu, ctx, f, dA, n, gu.dev(B), nrhs, solves - 1)
+    mpcr.mpcr_factor_destroy(f)
+    ref = np.linalg.solve(A, B)
+    assert np.linalg.norm(X - ref) <= 1e-12 * np.linalg.norm(ref)
