@@ -2195,42 +2195,65 @@ int mpcr_gemm(mpcr_ctx* ctx, mpcr_prec_t prec, int transA, int transB, int64_t m
     return MPCR_OK;
   }
   // 16/8-bit: the kernel reads op(A) as m x k and op(B) as n x k arrays with k
-  // contiguous, 16-byte aligned rows and whole stages of k; operands in another
-  // layout are packed into a workspace first (one pass over each, small next to
-  // the product), k padded with zeros.
+  // contiguous and 16-byte aligned rows.  Operands like that are read where they are,
+  // others are packed into a workspace first (one pass over each, small next to the
+  // product).  A ragged k: both are packed, k padded with zeros to whole stages, if
+  // both have to be, or one that is not the smaller (NN 8192 x 16 x 8208, FP8 113 us
+  // packed, 128 with B in place), or if the product is large enough for the kernel
+  // that takes whole stages only; else, or if there is no workspace for that, what is
+  // readable stays in place (TN 8192 x 16 x 8208 BF16 222 -> 175 us, 32768 x 16 x 8208
+  // 478 -> 211; FP8 107 -> 86, 296 -> 116).
   const int es = (p == F8) ? 1 : 2;
   const int64_t kst = gemm_lowp_kstage(p), kp = (k + kst - 1) / kst * kst;
-  auto usable = [&](const void* ptr, int64_t ld, bool kcontig) {
-    return kcontig && k == kp && ((uintptr_t)ptr % 16 == 0) && ((ld * es) % 16 == 0);
+  auto readable = [&](const void* ptr, int64_t ld, bool kcontig) {
+    return kcontig && ((uintptr_t)ptr % 16 == 0) && ((ld * es) % 16 == 0);
   };
-  const bool a_ok = usable(d_A, lda, transA != 0), b_ok = usable(d_B, ldb, transB == 0);
-  const int64_t a_bytes = a_ok ? 0 : (m * kp * es + 255) / 256 * 256, b_bytes = b_ok ? 0 : n * kp * es;
-  if (ctx->ws_gemm_bytes < a_bytes + b_bytes) {
+  const bool a_in = readable(d_A, lda, transA != 0), b_in = readable(d_B, ldb, transB == 0);
+  bool a_ok, b_ok;
+  int64_t kk, ldk, a_bytes, b_bytes;  // the kernel's k, the packed leading dimension
+  auto plan = [&](bool whole) {
+    a_ok = a_in && (!whole || k == kp);
+    b_ok = b_in && (!whole || k == kp);
+    kk = whole ? kp : k;
+    ldk = whole ? kp : (k + 15) / 16 * 16;
+    a_bytes = a_ok ? 0 : (m * ldk * es + 255) / 256 * 256;
+    b_bytes = b_ok ? 0 : n * ldk * es;
+    return ctx->ws_gemm_bytes >= a_bytes + b_bytes;
+  };
+  const bool whole = k == kp || (a_in ? !b_in && m <= n : !b_in || n <= m) || gemm_lowp_whole_stages(p, m, n, k);
+  if (!plan(whole)) {
     HIP_TRY(ctx, hipStreamSynchronize(s));
     dfree(ctx->arena, ctx->ws_gemm);
     ctx->ws_gemm = nullptr;
     ctx->ws_gemm_bytes = 0;
-    HIP_TRY(ctx, dmalloc(ctx->arena, &ctx->ws_gemm, (size_t)(a_bytes + b_bytes)));
+    hipError_t e = dmalloc(ctx->arena, &ctx->ws_gemm, (size_t)(a_bytes + b_bytes));
+    if (e == hipErrorOutOfMemory && whole && k != kp) {
+      (void)hipGetLastError();  // (or the next launch would report it)
+      ctx->ws_gemm = nullptr;
+      e = plan(false) ? hipSuccess : dmalloc(ctx->arena, &ctx->ws_gemm, (size_t)(a_bytes + b_bytes));
+    }
+    if (e != hipSuccess) ctx->ws_gemm = nullptr;
+    HIP_TRY(ctx, e);
     ctx->ws_gemm_bytes = a_bytes + b_bytes;
   }
   const void* A = d_A;
   int64_t ldat = lda;
   if (!a_ok) {
     A = ctx->ws_gemm;
-    ldat = kp;
-    HIP_TRY(ctx, launch_pack(es, transA == 0, m, k, d_A, lda, ctx->ws_gemm, kp, s));
+    ldat = ldk;
+    HIP_TRY(ctx, launch_pack(es, transA == 0, m, k, d_A, lda, ctx->ws_gemm, ldk, s));
   }
   const void* B = d_B;
   int64_t ldbk = ldb;
   if (!b_ok) {
     B = ctx->ws_gemm + a_bytes;
-    ldbk = kp;
-    HIP_TRY(ctx, launch_pack(es, transB != 0, n, k, d_B, ldb, ctx->ws_gemm + a_bytes, kp, s));
+    ldbk = ldk;
+    HIP_TRY(ctx, launch_pack(es, transB != 0, n, k, d_B, ldb, ctx->ws_gemm + a_bytes, ldk, s));
   }
   // FP8 scale grids belong to the stored matrices (column-major over 128 x 128 blocks)
   const int64_t mbA = transA ? (k + 127) / 128 : (m + 127) / 128;
   const int64_t mbB = transB ? (n + 127) / 128 : (k + 127) / 128;
-  HIP_TRY(ctx, launch_gemm_lowp(p, m, n, kp, alpha, A, ldat, d_scaleA_exp, mbA, transA != 0, B, ldbk, d_scaleB_exp,
+  HIP_TRY(ctx, launch_gemm_lowp(p, m, n, kk, alpha, A, ldat, d_scaleA_exp, mbA, transA != 0, B, ldbk, d_scaleB_exp,
                                 mbB, transB != 0, beta, d_C, ldc, cp, s));
   return MPCR_OK;
 }

@@ -255,10 +255,11 @@ k_gemm(int64_t M, int64_t N, int64_t K, double alpha, const void* Av, int64_t ld
 // ---------------------------------------------------------------------------
 // 16- and 8-bit path.  Both operands are read "k-contiguous": A as an m x k
 // row-major array (AT, leading dimension ldat) and B as the usual k x n
-// column-major array, with 16-byte aligned rows and k a multiple of the stage.
-// Operands in another layout are first packed into that one, k padded with
-// zeros (k_pack); rows past m or n are read as the last row and their products
-// not stored, so ragged and whole shapes run the same loop.
+// column-major array, with 16-byte aligned rows.  Operands in another layout are
+// first packed into that one, k padded with zeros to whole stages (k_pack); rows
+// past m or n are read as the last row and their products not stored, so ragged and
+// whole shapes run the same loop.  A part of a stage at the end of k (TAIL: operands
+// that are read where they are) is loaded behind the loop, zeros past the last k.
 //
 // One workgroup of WM x WN waves computes a (16 TA WM) x (16 TB WN) block of C,
 // a wave TA x TB tiles of 16 x 16.  Stages of 128 bytes of k: both operands'
@@ -331,7 +332,7 @@ __device__ __forceinline__ void lowp_store(const f4 (&acc)[TA][TB], double alpha
   }
 }
 
-template <int P, int WM, int WN, int TA, int TB, int PAD>
+template <int P, int WM, int WN, int TA, int TB, int PAD, bool TAIL>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N, int64_t K, double alpha,
                                                             const void* ATv, int64_t ldat, const int8_t* sA,
                                                             int64_t mbA, int sa_kmajor, const void* Bv, int64_t ldb,
@@ -392,13 +393,33 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
 #pragma unroll
     for (int b = 0; b < TB; ++b) acc[a][b] = f4{0, 0, 0, 0};
 
-  const int64_t KB = K * ES;
-  if (K > 0) {
+  const int64_t KB = TAIL ? K / BK * STAGE : K * ES;  // (whole stages, in bytes)
+  if (KB > 0) {
     gload(0);
     sstore(0);
   }
   __syncthreads();
   int cur = 0;
+  // the part of a stage behind the whole ones into the buffer that nobody reads any more
+  auto load_tail = [&] {
+    using E = std::conditional_t<ES == 1, uint8_t, uint16_t>;
+    const int left = (int)(K * ES - KB) - lchunk * 16;  // bytes of this thread's vectors
+    auto vec = [&](const uint8_t* p) {
+      u32x4 v = {0, 0, 0, 0};
+      if (left >= 16) return *(const u32x4*)p;
+#pragma unroll
+      for (int e = 0; e < 16 / ES; ++e)
+        if (e * ES < left) v[e * ES / 4] |= (uint32_t)((const E*)p)[e] << (8 * ES * (e % (4 / ES)));
+      return v;
+    };
+#pragma unroll
+    for (int v = 0; v < NVA; ++v) ga[v] = vec(pa[v] + KB);
+#pragma unroll
+    for (int v = 0; v < NVB; ++v) gb[v] = vec(pb[v] + KB);
+    sstore(cur ^ 1);
+    __syncthreads();
+    cur ^= 1;
+  };
   if constexpr (P == F8) {
     auto frag = [&](const uint8_t* p) {  // 32 consecutive bytes
       const u32x4 lo = *(const u32x4*)p, hi = *(const u32x4*)(p + 16);
@@ -413,12 +434,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
     const int8_t* peb = sb_kmajor ? sB + jb : sB + jb * mbB;
     const int64_t dea = sa_kmajor ? 1 : mbA, deb = sb_kmajor ? mbB : 1;
     int nea = KB > 0 ? *pea : 0, neb = KB > 0 ? *peb : 0;
-    for (int64_t k0 = 0; k0 < KB; k0 += STAGE) {
-      const int64_t kn = k0 + STAGE < KB ? k0 + STAGE : k0;
-      const int ea = nea, eb = neb;
-      nea = pea[(kn / 128) * dea];
-      neb = peb[(kn / 128) * deb];
-      gload(kn);
+    auto mma = [&](int ea, int eb) {
       // E8M0 scale bytes of 2^-ea and 2^-eb; 255 (ea = -128) is no scale: one step goes to the other operand's
       int sca = 127 - ea, scb = 127 - eb;
       if (sca > 254) { sca = 254; scb = scb < 254 ? scb + 1 : 254; }
@@ -437,9 +453,22 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
           acc[a][b] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fb[b], fa, acc[a][b], 0, 0, 0, scb, 0, sca);
         fa = fan;
       }
+    };
+    for (int64_t k0 = 0; k0 < KB; k0 += STAGE) {
+      const int64_t kn = k0 + STAGE < KB ? k0 + STAGE : k0;
+      const int ea = nea, eb = neb;
+      nea = pea[(kn / 128) * dea];
+      neb = peb[(kn / 128) * deb];
+      gload(kn);
+      mma(ea, eb);
       sstore(cur ^ 1);
       __syncthreads();
       cur ^= 1;
+    }
+    if constexpr (TAIL) {
+      const int ea = pea[(KB / 128) * dea], eb = peb[(KB / 128) * deb];
+      load_tail();
+      mma(ea, eb);
     }
   } else {
     // fragments of one 32-wide k step: A rows 16 a + g16, B columns 16 b + g16,
@@ -470,7 +499,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
     // to the other LDS buffer at its end; the second step's fragments are read
     // while the first step's MFMAs run; after the barrier the next stage's first
     // fragments are read
-    if (K > 0) frag(0, 0, fa0, fb0);
+    if (KB > 0) frag(0, 0, fa0, fb0);
     for (int64_t k0 = 0; k0 < KB; k0 += STAGE) {
       gload(k0 + STAGE < KB ? k0 + STAGE : k0);
       frag(cur, 32, fa1, fb1);
@@ -480,6 +509,13 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
       __syncthreads();
       cur ^= 1;
       frag(cur, 0, fa0, fb0);
+    }
+    if constexpr (TAIL) {
+      load_tail();
+      frag(cur, 0, fa0, fb0);
+      frag(cur, 32, fa1, fb1);
+      mma(fa0, fb0);
+      mma(fa1, fb1);
     }
   }
 
@@ -676,25 +712,34 @@ static bool large_blocks(int64_t m, int64_t n) {
 // eight waves 167; x 512: 110 and 111; x 256: 90 and 81; x 64: 69 and 63).  Its
 // copies hold 63 rows of an operand in a 32-bit offset.
 static bool big_blocks(int prec, int64_t m, int64_t n, int64_t k, int64_t ld) {
-  return prec != F8 && ((m + 127) / 128) * ((n + 127) / 128) > 512 && k >= 512 && ld <= (INT64_C(1) << 25);
+  return prec != F8 && k % (STAGE / 2) == 0 && ((m + 127) / 128) * ((n + 127) / 128) > 512 && k >= 512 && ld <= (INT64_C(1) << 25);
 }
 
-// k per stage of the 16/8-bit product: its operands' k is a multiple of it
+// k per stage of the 16/8-bit product
 int gemm_lowp_kstage(int prec) { return STAGE / (prec == F8 ? 1 : 2); }
+
+bool gemm_lowp_whole_stages(int prec, int64_t m, int64_t n, int64_t k) {
+  const int64_t st = gemm_lowp_kstage(prec), kp = (k + st - 1) / st * st;
+  return big_blocks(prec, m, n, kp, kp);
+}
 
 hipError_t launch_gemm_lowp(int prec, int64_t m, int64_t n, int64_t k, double alpha, const void* AT, int64_t ldat,
                             const int8_t* sA, int64_t mbA, int sa_kmajor, const void* B, int64_t ldb,
                             const int8_t* sB, int64_t mbB, int sb_kmajor, double beta, void* C, int64_t ldc, int cprec,
                             hipStream_t s) {
   const int es = prec == F8 ? 1 : 2;
-  if (k % (STAGE / es) != 0 || (ldat * es) % 16 != 0 || (ldb * es) % 16 != 0 || (uintptr_t)AT % 16 != 0 ||
+  const bool tail = k % (STAGE / es) != 0;
+  if ((ldat * es) % 16 != 0 || (ldb * es) % 16 != 0 || (uintptr_t)AT % 16 != 0 ||
       (uintptr_t)B % 16 != 0)
     return hipErrorInvalidValue;
-#define MPCR_LOWP(P, WM, WN, TA, TB, PAD)                                                                             \
-  k_gemm_lowp<P, WM, WN, TA, TB, PAD>                                                                                 \
+#define MPCR_LOWP_T(P, WM, WN, TA, TB, PAD, TAIL)                                                                     \
+  k_gemm_lowp<P, WM, WN, TA, TB, PAD, TAIL>                                                                           \
       <<<dim3((unsigned)((m + 16 * TA * WM - 1) / (16 * TA * WM)), (unsigned)((n + 16 * TB * WN - 1) / (16 * TB * WN))), \
          64 * WM * WN, 0, s>>>(m, n, k, alpha, AT, ldat, sA, mbA, sa_kmajor, B, ldb, sB, mbB, sb_kmajor, beta, C, ldc, \
                                cprec)
+#define MPCR_LOWP(P, WM, WN, TA, TB, PAD)                \
+  if (tail) MPCR_LOWP_T(P, WM, WN, TA, TB, PAD, true);   \
+  else MPCR_LOWP_T(P, WM, WN, TA, TB, PAD, false)
   if (big_blocks(prec, m, n, k, ldat > ldb ? ldat : ldb)) {
     const dim3 grid((unsigned)((m + LOWP_BIG - 1) / LOWP_BIG), (unsigned)((n + LOWP_BIG - 1) / LOWP_BIG));
     if (prec == BF16) k_gemm_lowp_big<BF16><<<grid, 256, 0, s>>>(m, n, k, alpha, AT, ldat, B, ldb, beta, C, ldc, cprec);
@@ -715,6 +760,7 @@ hipError_t launch_gemm_lowp(int prec, int64_t m, int64_t n, int64_t k, double al
     }
   }
 #undef MPCR_LOWP
+#undef MPCR_LOWP_T
   return hipGetLastError();
 }
 

@@ -393,7 +393,9 @@ hipError_t launch_gemm(int prec, int transA, int transB, int64_t m, int64_t n, i
                        int cprec, hipStream_t s);
 hipError_t launch_pack(int es, int trans, int64_t rows, int64_t cols, const void* in, int64_t ldi, void* out,
                        int64_t ldo, hipStream_t s);
-int gemm_lowp_kstage(int prec);  // k of the 16/8-bit product's operands is a multiple of this
+int gemm_lowp_kstage(int prec);  // k per stage of the 16/8-bit product
+// whether it wants the operands' k in whole stages (padded with zeros) even if that means packing them
+bool gemm_lowp_whole_stages(int prec, int64_t m, int64_t n, int64_t k);
 hipError_t launch_gemm_lowp(int prec, int64_t m, int64_t n, int64_t k, double alpha, const void* AT, int64_t ldat,
                             const int8_t* sA, int64_t mbA, int sa_kmajor, const void* B, int64_t ldb,
                             const int8_t* sB, int64_t mbB, int sb_kmajor, double beta, void* C, int64_t ldc, int cprec,
