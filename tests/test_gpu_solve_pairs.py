@@ -108,3 +108,22 @@ def test_large_tiles(g, nb, n, solves, nrhs):
     mpcr.mpcr_factor_destroy(f)
     ref = np.linalg.solve(A, B)
     assert np.linalg.norm(X - ref) <= 1e-12 * np.linalg.norm(ref)
+
+
+# one call that factors the same store again and solves in between: the Newton steps of the Laplace
+# approximation, whose second and later solves must not use pairs of an earlier step's factor.  (With the
+# second step's pairs kept, the last range's mode is off by 2e-3 to 3e-3 at these sizes; right, the two
+# Newton iterations agree to 1e-8, the square root of the stopping rule's 1e-12 being their last step, which
+# converges quadratically.)
+@pytest.mark.parametrize("nb,n", [(128, 300), (128, 400), (256, 900)])
+def test_pairs_of_a_store_factored_again(g, nb, n):
+    gu, ctx = g
+    from oracle import laplace
+    from tests.test_gpu_laplace import inla_data, run
+    locs, y = inla_data(n, 43)
+    alphas = np.array([0.1, 0.5, 0.9])
+    lp, _, its, mode = run(gu, ctx, locs, y, alphas, m=lower_map((n + nb - 1) // nb, 0), nb=nb)
+    ref = [laplace.laplace_logpost(locs, y, 0.1, a, 0.5, 10.0) for a in alphas]
+    assert its == [r["iters"] for r in ref] and min(its) >= 4
+    np.testing.assert_allclose(mode, ref[-1]["mode"], rtol=0, atol=1e-8)
+    np.testing.assert_allclose(lp, [r["lpost"] for r in ref], rtol=1e-9)
