@@ -30,7 +30,6 @@ CFLAGS = [
 ]
 # roctx ranges (rocprofiler-sdk)
 LINK_FLAGS = ["-L/opt/rocm/lib", "-lrocprofiler-sdk-roctx"]
-LD = os.environ.get("LD_LLD", "/opt/rocm/llvm/bin/ld.lld")
 # the factorisation's kernels: three sources compiled side by side (the slowest of
 # the library), joined into the one object factor.o
 FACTOR_PARTS = ["update.hip", "factor.hip", "panel.hip"]
@@ -51,6 +50,15 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _linker() -> str:
+    """The linker that joins relocatable objects: LD_LLD, else ROCm's, else the system's."""
+    names = [os.environ["LD_LLD"]] if "LD_LLD" in os.environ else ["/opt/rocm/llvm/bin/ld.lld", "ld.lld", "ld"]
+    for name in names:
+        if shutil.which(name):
+            return name
+    raise RuntimeError(f"linker not found: {', '.join(names)}")
+
+
 def _link(cmd: list) -> None:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -60,12 +68,13 @@ def _link(cmd: list) -> None:
 def build(jobs: int = 8) -> str:
     if not shutil.which(HIPCC) and not os.path.exists(HIPCC):
         raise RuntimeError("hipcc not found")
+    ld = _linker()
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, SOURCES))
     parts, objs = objs[:len(FACTOR_PARTS)], objs[len(FACTOR_PARTS):]
     factor = os.path.join(BUILD, "factor.o")
-    _link([LD, "-r", *parts, "-o", factor])
+    _link([ld, "-r", *parts, "-o", factor])
     tmp = LIB + ".tmp"
     _link([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", factor, *objs, *LINK_FLAGS, "-o", tmp])
     os.replace(tmp, LIB)
