@@ -434,7 +434,14 @@ int make_factor(mpcr_ctx* ctx, int64_t n, int64_t nb, const std::vector<uint8_t>
 // 3072 1850 and 1757 with tiles of 256, 1807 and 1730 with 512; 4096 2577 and 2563;
 // 6000 4360 and 4500).
 constexpr int64_t LOOKAHEAD_MIN_N = 3072;
-constexpr int64_t COL_STREAM_MIN_NT = 32;  // more tiles per dimension than this: next column on its own stream
+// More tiles per dimension than this: next column, and the updates below FP64, on
+// streams of their own.  Factor alone on the GPU, one stream less -> own streams, FP64
+// within 1.5% either way (10000: 9.64 and 9.69 ms); tiles of 256 and 512, FP32 beyond
+// the first off-diagonal: n = 4000 2.24 -> 2.02 ms, 7919 4.91 -> 4.43, 9000 6.06 ->
+// 5.41, 12000 (256) 9.28 -> 8.42, (512) 10.6 -> 9.6, 18000 23.2 -> 21.5.  The line
+// keeps the serving sizes (n <= 8192, tiles of 256), whose slots share the process's
+// hardware queues, at two streams a slot.
+constexpr int64_t COL_STREAM_MIN_NT = 32;
 
 int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
   hipStream_t P = ctx->stream;
@@ -443,9 +450,8 @@ int run_factorisation(mpcr_ctx* ctx, mpcr_factor* f) {
   ++f->version;
   const double nb3 = (double)f->nb * f->nb * f->nb;
   const int64_t nt = f->nt;
-  // the column stream pays off once the trailing updates are long enough to
-  // hide POTRF(k+1) behind; small factorisations (serving) keep the next
-  // column on P, which then runs POTRF(k), TRSM(k) and the whole column k+1
+  // small factorisations (serving) keep the next column on P, which then runs
+  // POTRF(k), TRSM(k) and the whole column k+1
   const bool use_col = nt > COL_STREAM_MIN_NT;  // (tiles are 128 at least: more than LOOKAHEAD_MIN_N)
   const bool ahead = f->N > LOOKAHEAD_MIN_N;
   if (ahead) HIP_TRY(ctx, ensure_lookahead(ctx, (size_t)(4 * nt + 2), use_col));

@@ -536,7 +536,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_lowp(int64_t M, int64_t N
 // A copy of 1 KB is 8 rows of 128 bytes; granule c of row r is kept at c ^ (r % 8),
 // so that the 16 rows of a fragment read spread over the banks.  Every element
 // takes its products in the order of the 128 x 128 blocks: the same bits.
-// Whole calls, before (eight waves) -> after: BF16 NN 8192^3 1122 -> 925 us,
+// Whole calls, before (eight waves) -> after: BF16 NN 8192^3 1122 -> 904 to 925 us,
 // TN 1154 -> 935, FP16 1148 -> 947, BF16 4096^3 151 -> 117, 16384 x 4096 x 2048
 // 321 -> 266.  An FP8 form (two sets of eight 32-byte fragments) spills: 2349 us
 // for 612.
@@ -694,8 +694,8 @@ hipError_t launch_pack(int es, int trans, int64_t rows, int64_t cols, const void
   return hipGetLastError();
 }
 
-// 256 x 256 blocks (half the LDS traffic per product of the 128 x 128 ones; eight
-// waves of 128 x 64) once they fill the chip; a launch that leaves more than a
+// 256 x 256 blocks (two thirds of the LDS traffic per product of the 128 x 128 ones:
+// half the stores, three quarters of the fragment reads; eight waves of 128 x 64) once they fill the chip; a launch that leaves more than a
 // fifth of its last round of 256 CUs idle runs 128 x 128 blocks (four waves of 64 x
 // 64, two workgroups per CU).
 static bool large_blocks(int64_t m, int64_t n) {
@@ -709,7 +709,10 @@ static bool large_blocks(int64_t m, int64_t n) {
 // and 128 us; 4100: 219 and 276; 5120: 229 and 383; 5888: 379 and 548; small ones
 // 23 and big ones 27 us at 2816 x 2816 x 128).  Its one wave per SIMD starts and
 // ends with nothing beside it, which pays from k = 512 (8192 x 8192 x 1024: 152 us,
-// eight waves 167; x 512: 110 and 111; x 256: 90 and 81; x 64: 69 and 63).  Its
+// eight waves 167; x 512: 110 and 111; x 256: 90 and 81; x 64: 69 and 63).  Long thin
+// shapes, whole calls, against the 128 x 128 or whole-block kernels that came before
+// it: 65536 x 130 x 1024 157 -> 52 us, 131072 x 64 x 512 91 -> 62, x 4096 645 -> 241, 16
+// x 131072 x 1024 156 -> 87, 33000 x 257 x 1024 151 -> 68, 65536 x 256 x 1024 61 -> 52.  Its
 // copies hold 63 rows of an operand in a 32-bit offset.
 static bool big_blocks(int prec, int64_t m, int64_t n, int64_t k, int64_t ld) {
   return prec != F8 && k % (STAGE / 2) == 0 && ((m + 127) / 128) * ((n + 127) / 128) > 512 && k >= 512 && ld <= (INT64_C(1) << 25);

@@ -488,7 +488,7 @@ hipError_t launch_potrf_block(const TileView& tv, int k, int j, double* dinv, hi
 }
 
 // ---------------------------------------------------------------------------
-// Shared pieces of the diagonal-tile POTRF and the panel TRSM.
+// Panel solves and inverses of tiles above 512 (k_trsm, k_trsm4, k_trtri).
 // ---------------------------------------------------------------------------
 // acc0/acc1 (16 x 16 each) += A[R0.., K0:K1] * B[C0.., K0:K1]^T, operands read
 // straight from column-major FP64 storage (lda = ldb = ld).  Software

@@ -705,7 +705,17 @@ __global__ __launch_bounds__(512) void k_update_split_big(TileView tv, int k, co
   }
 }
 
-constexpr int SPLIT_BIG_MIN = 512;  // 128 x 128 blocks from which the 256 x 128 kernel is used
+// 128 x 128 blocks from which the 256 x 128 kernel is used.  A round of either is 512
+// such blocks (two workgroups per CU of the small kernel, one of the big).  Launches
+// alone, small -> big, 512-tiles: up to 256 blocks the small one, whose workgroups
+// then have a CU each (128: 29 -> 38 us, 256: 33 -> 44); 272 to 512 the big one (320:
+// 51 -> 47, 448: 49 -> 45); in the second round first the small one (576: 70 -> 78,
+// 720: 72 -> 80), then the big one (880: 91 -> 83), and so on with less and less
+// between them (1056: 112 -> 118, 1456: 139 -> 130, 2176: 213 -> 209, 2448: 239 ->
+// 225, 3696: 374 -> 361; 256- and 1024-tiles alike).  No one line fits: at 512 the
+// wrong one costs about a tenth of a launch below 0.1 ms, and the long launches get
+// the big one.
+constexpr int SPLIT_BIG_MIN = 512;
 
 hipError_t launch_tile_update_packed(const TileView& tv, int k, int cfmt, const GemmTask* tasks, int ntasks,
                                      const uint16_t* planes, hipStream_t s) {
